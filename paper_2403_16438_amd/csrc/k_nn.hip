@@ -1404,27 +1404,6 @@ __global__ void k_bias_act(float* __restrict__ Y, const float* __restrict__ bias
   Y[i] = relu ? fmaxf(v, 0.f) : v;
 }
 
-// dY *= [Y > 0] (ReLU backward through the stored output)
-__global__ void k_relu_bwd(float* __restrict__ dY, const float* __restrict__ Y, long long n) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !(Y[i] > 0.f)) dY[i] = 0.f;
-}
-
-// db[c] (+)= sum_n dY[c][n], one block per channel, fixed order
-__global__ void k_bias_grad(const float* __restrict__ dY, float* __restrict__ db, long long N, int accumulate) {
-  __shared__ float sh[256];
-  const int c = blockIdx.x;
-  float s = 0.f;
-  for (long long n = threadIdx.x; n < N; n += 256) s += dY[(long long)c * N + n];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) db[c] = accumulate ? db[c] + sh[0] : sh[0];
-}
-
 // 2x2 max pool (H, W even): Y[c][b][i][j] = max over the 2x2 block; arg = 0..3
 __global__ void k_pool(const float* __restrict__ X, float* __restrict__ Y, uint8_t* __restrict__ arg, int CB,
                        int H, int W) {
@@ -1850,10 +1829,6 @@ void col2im1(const float* dcol, float* din, int C, int Tin, int Tout, int KT, in
 }
 void bias_act(float* Y, const float* b, int C, long long N, bool relu, hipStream_t st) {
   L1(k_bias_act, (long long)C * N, Y, b, C, N, (int)relu);
-}
-void relu_bwd(float* dY, const float* Y, long long n, hipStream_t st) { L1(k_relu_bwd, n, dY, Y, n); }
-void bias_grad(const float* dY, float* db, int C, long long N, hipStream_t st) {
-  hipLaunchKernelGGL(k_bias_grad, dim3(C), dim3(256), 0, st, dY, db, N, 0);
 }
 void pool(const float* X, float* Y, uint8_t* arg, int CB, int H, int W, hipStream_t st) {
   L1(k_pool, (long long)CB * (H / 2) * (W / 2), X, Y, arg, CB, H, W);

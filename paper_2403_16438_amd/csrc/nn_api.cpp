@@ -83,6 +83,8 @@ struct Plan {
   Buf wb, grad, vel;   // BF16 weights, FP32 gradients, RMSProp state
   Buf wr;              // 3 x 3 convolution weights reordered for the direct kernel
   size_t wr_off[NPAR]; // element offset of each 3 x 3 layer in wr
+  Buf wd;              // and for its input gradient (reorder_dx), the same offsets
+  Buf part, bpart;     // partial sums of the weight and bias gradients
   size_t total;
 };
 
@@ -164,6 +166,17 @@ Plan make_plan(int B, int H, int W, bool st) {
         at_wr += (conv3_reordered_size(P[i].rows, P[i].cols / 9) + 7) / 8 * 8;
     }
     p.wr = take(2 * at_wr);
+    p.wd = take(2 * at_wr);
+    // pixels that each layer's weight gradient sums over
+    const long long full[NPAR] = {10 * N, 5 * N, N, N, N, N2, N2, N4, N4, N4, N2, N2, N2, N, N, N};
+    size_t at_part = 0, channels = 0;
+    for (int i = 0; i < NPAR; ++i) {
+      const long long z = std::min<long long>(kGradSplits, (full[i] + 31) / 32);
+      at_part += ((size_t)z * P[i].rows * P[i].cols + 3) / 4 * 4;
+      channels += bias_len(P, i);
+    }
+    p.part = take(f * at_part);
+    p.bpart = take(f * 256 * channels);
   }
   p.grad = take(f * po.total);
   p.vel = take(f * po.total);
@@ -196,12 +209,13 @@ const float* bias(seg_nn* n, int id) { return n->params + n->po.b[id]; }
 // refreshes the reordered copy of every 3 x 3 convolution's BF16 weights
 void reorder_conv3(seg_nn* n, hipStream_t st) {
   for (int id = E1A; id < NPAR; ++id)
-    if (id != U2 && id != U1 && id != FO)
-      conv3_reorder(wbf(n, id), at<uint16_t>(n, n->plan.wr) + n->plan.wr_off[id], n->P[id].rows,
-                    n->P[id].cols / 9, st);
+    if (id != U2 && id != U1 && id != FO) {
+      const int Co = n->P[id].rows, Ci = n->P[id].cols / 9;
+      conv3_reorder(wbf(n, id), at<uint16_t>(n, n->plan.wr) + n->plan.wr_off[id], Co, Ci, st);
+      if (Ci % 32 == 0) reorder_dx(wbf(n, id), at<uint16_t>(n, n->plan.wd) + n->plan.wr_off[id], Co, Ci, st);
+    }
 }
 float* gw(seg_nn* n, int id) { return at<float>(n, n->plan.grad) + n->po.w[id]; }
-float* gb(seg_nn* n, int id) { return at<float>(n, n->plan.grad) + n->po.b[id]; }
 
 hipError_t gemm_wx(seg_nn* n, int id, const void* X, bool x_bf16, long long ncols, float* Y, hipStream_t st) {
   // Y [rows][ncols] = W [rows][cols] X [cols][ncols]
@@ -276,22 +290,70 @@ hipError_t conv3(seg_nn* n, int id, const float* X, int Bn, int H, int W, float*
   return e;
 }
 
-// backward of conv3: dY (modified in place by the ReLU mask), weight and bias
-// gradients, input gradient into dX (accumulated when acc)
-hipError_t conv3_bwd(seg_nn* n, int id, const float* X, const float* Y, float* dY, int Bn, int H, int W,
-                     float* dX, bool acc, bool relu, hipStream_t st) {
+// The gradients of a backward pass: the layers whose sums over pixels are
+// added at its end by grad_reduce, and what is left of the partial sums' space.
+struct Grads {
+  GradTable t{};
+  float* part;
+  float* bpart;
+  int channels = 0;
+  Grads(seg_nn* n) : part(at<float>(n, n->plan.part)), bpart(at<float>(n, n->plan.bpart)) { t.bpart = bpart; }
+  // a bias gradient of C channels: where its chains go
+  float* bias(seg_nn* n, int id) {
+    float* p = bpart + (size_t)channels * 256;
+    const int C = bias_len(n->P, id);
+    t.b[t.nb++] = BiasSeg{(long long)n->po.b[id], C, channels};
+    channels += C;
+    return p;
+  }
+  // a weight gradient [M][C T] whose partial sums were launched at `part`
+  void weight(seg_nn* n, int id, int T, long long K) {
+    const int M = n->P[id].rows, C = n->P[id].cols / T, Z = grad_ranges(K);
+    t.w[t.nw++] = GradSeg{part, (long long)n->po.w[id], M, C, T, Z, t.wblocks};
+    t.wblocks += (M * C * T + 255) / 256;
+    part += ((size_t)Z * M * C * T + 3) / 4 * 4;
+  }
+};
+
+// weight gradient dW = dY X^T of a layer whose product rows are rows of X
+hipError_t lin_dw(seg_nn* n, Grads& g, int id, const float* dY, const float* X, long long K, hipStream_t st) {
+  if (dw1(dY, X, g.part, n->P[id].rows, n->P[id].cols, K, 1, 1, 0, 0, K, st)) {
+    g.weight(n, id, 1, K);
+    return hipSuccess;
+  }
+  return gemm_dw(n, id, dY, X, false, K, st);
+}
+
+// the same of a temporal convolution with input X [C][Tin][N]
+hipError_t temporal_dw(seg_nn* n, Grads& g, int id, const float* dY, const float* X, int C, int Tin, int Tout, int S,
+                       int Pd, long long N, hipStream_t st) {
+  if (dw1(dY, X, g.part, n->P[id].rows, n->P[id].cols, Tout * N, Tin, 5, S, Pd, N, st)) {
+    g.weight(n, id, 1, Tout * N);
+    return hipSuccess;
+  }
+  uint16_t* col = at<uint16_t>(n, n->plan.col);
+  im2col1(X, col, C, Tin, Tout, 5, S, Pd, N, st);
+  return gemm_dw(n, id, dY, col, true, Tout * N, st);
+}
+
+// backward of conv3 once dY is masked and its bias gradient taken: weight
+// gradient, and the input gradient into dX unless it is null
+hipError_t conv3_bwd(seg_nn* n, Grads& g, int id, const float* X, const float* dY, int Bn, int H, int W, float* dX,
+                     hipStream_t st) {
   const int Ci = n->P[id].cols / 9, Co = n->P[id].rows;
   const long long N = (long long)Bn * H * W;
-  if (relu) relu_bwd(dY, Y, (long long)Co * N, st);
-  bias_grad(dY, gb(n, id), Co, N, st);
-  uint16_t* col = at<uint16_t>(n, n->plan.col);
-  im2col3(X, col, Ci, Bn, H, W, st);
-  hipError_t e = gemm_dw(n, id, dY, col, true, N, st);
-  if (e != hipSuccess) return e;
-  if (!dX) return hipSuccess;
+  hipError_t e = hipSuccess;
+  if (dw3(dY, X, g.part, Co, Ci, Bn, H, W, st)) {
+    g.weight(n, id, 9, N);
+  } else {
+    uint16_t* col = at<uint16_t>(n, n->plan.col);
+    im2col3(X, col, Ci, Bn, H, W, st);
+    if ((e = gemm_dw(n, id, dY, col, true, N, st)) != hipSuccess) return e;
+  }
+  if (!dX || dx3(at<uint16_t>(n, n->plan.wd) + n->plan.wr_off[id], dY, dX, Co, Ci, Bn, H, W, st, &e)) return e;
   float* dcol = at<float>(n, n->plan.dcol);
   e = gemm_wtdy(n, id, dY, N, dcol, st);
-  col2im3(dcol, dX, Ci, Bn, H, W, acc, st);
+  col2im3(dcol, dX, Ci, Bn, H, W, false, st);
   return e;
 }
 
@@ -467,50 +529,56 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   auto chk = [&](hipError_t x) {
     if (x != hipSuccess && e == hipSuccess) e = x;
   };
+  Grads g(n);
   float* gl = at<float>(n, p.glogit);
   float* d1 = at<float>(n, p.d1);
   float* gd1 = at<float>(n, p.gd1);
-  // output 1x1
-  bias_grad(gl, gb(n, FO), 1, N, st);
-  chk(gemm_dw(n, FO, gl, d1, false, N, st));
-  chk(gemm_wtdy(n, FO, gl, N, gd1, st));
+  // output 1x1, and what it passes down
+  bias_mask(gl, nullptr, g.bias(n, FO), 1, N, st);
+  chk(lin_dw(n, g, FO, gl, d1, N, st));
+  bias_outer(gl, wbf(n, FO), gd1, d1, g.bias(n, D1B), n->P[FO].cols, N, st);
   // d1b, d1a
   float* d1a = at<float>(n, p.d1a);
   float* gd1a = at<float>(n, p.gd1a);
   float* cat1 = at<float>(n, p.cat1);
   float* gcat1 = at<float>(n, p.gcat1);
-  chk(conv3_bwd(n, D1B, d1a, d1, gd1, Bn, H, W, gd1a, false, true, st));
-  chk(conv3_bwd(n, D1A, cat1, d1a, gd1a, Bn, H, W, gcat1, false, true, st));
+  chk(conv3_bwd(n, g, D1B, d1a, gd1, Bn, H, W, gd1a, st));
+  bias_mask(gd1a, d1a, g.bias(n, D1A), n->P[D1A].rows, N, st);
+  chk(conv3_bwd(n, g, D1A, cat1, gd1a, Bn, H, W, gcat1, st));
   // u1: channels 0..31 of cat1 came from the transposed convolution
   float* gz1 = at<float>(n, p.gz1);
   float* d2 = at<float>(n, p.d2);
   float* gd2 = at<float>(n, p.gd2);
-  bias_grad(gcat1, gb(n, U1), 32, N, st);
+  bias_mask(gcat1, nullptr, g.bias(n, U1), 32, N, st);
   up_gather(gcat1, gz1, 32, Bn, H / 2, W / 2, st);
-  chk(gemm_dw(n, U1, gz1, d2, false, N2, st));
+  chk(lin_dw(n, g, U1, gz1, d2, N2, st));
   chk(gemm_wtdy(n, U1, gz1, N2, gd2, st));
   // d2b, d2a
   float* d2a = at<float>(n, p.d2a);
   float* gd2a = at<float>(n, p.gd2a);
   float* cat2 = at<float>(n, p.cat2);
   float* gcat2 = at<float>(n, p.gcat2);
-  chk(conv3_bwd(n, D2B, d2a, d2, gd2, Bn, H / 2, W / 2, gd2a, false, true, st));
-  chk(conv3_bwd(n, D2A, cat2, d2a, gd2a, Bn, H / 2, W / 2, gcat2, false, true, st));
+  bias_mask(gd2, d2, g.bias(n, D2B), n->P[D2B].rows, N2, st);
+  chk(conv3_bwd(n, g, D2B, d2a, gd2, Bn, H / 2, W / 2, gd2a, st));
+  bias_mask(gd2a, d2a, g.bias(n, D2A), n->P[D2A].rows, N2, st);
+  chk(conv3_bwd(n, g, D2A, cat2, gd2a, Bn, H / 2, W / 2, gcat2, st));
   // u2: channels 0..63 of cat2
   float* gz2 = at<float>(n, p.gz2);
   float* b3 = at<float>(n, p.b3);
   float* gb3 = at<float>(n, p.gb3);
-  bias_grad(gcat2, gb(n, U2), 64, N2, st);
+  bias_mask(gcat2, nullptr, g.bias(n, U2), 64, N2, st);
   up_gather(gcat2, gz2, 64, Bn, H / 4, W / 4, st);
-  chk(gemm_dw(n, U2, gz2, b3, false, N4, st));
+  chk(lin_dw(n, g, U2, gz2, b3, N4, st));
   chk(gemm_wtdy(n, U2, gz2, N4, gb3, st));
   // bottleneck
   float* e3a = at<float>(n, p.e3a);
   float* ge3a = at<float>(n, p.ge3a);
   float* p2 = at<float>(n, p.p2);
   float* gp2 = at<float>(n, p.gp2);
-  chk(conv3_bwd(n, E3B, e3a, b3, gb3, Bn, H / 4, W / 4, ge3a, false, true, st));
-  chk(conv3_bwd(n, E3A, p2, e3a, ge3a, Bn, H / 4, W / 4, gp2, false, true, st));
+  bias_mask(gb3, b3, g.bias(n, E3B), n->P[E3B].rows, N4, st);
+  chk(conv3_bwd(n, g, E3B, e3a, gb3, Bn, H / 4, W / 4, ge3a, st));
+  bias_mask(ge3a, e3a, g.bias(n, E3A), n->P[E3A].rows, N4, st);
+  chk(conv3_bwd(n, g, E3A, p2, ge3a, Bn, H / 4, W / 4, gp2, st));
   // skip 2 = channels 64..127 of cat2: its gradient is the concat part plus the pool path
   float* gs2 = gcat2 + 64 * N2;
   pool_bwd(gp2, at<uint8_t>(n, p.arg2), gs2, 64 * Bn, H / 2, W / 2, true, st);
@@ -518,42 +586,43 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* ge2a = at<float>(n, p.ge2a);
   float* p1 = at<float>(n, p.p1);
   float* gp1 = at<float>(n, p.gp1);
-  chk(conv3_bwd(n, E2B, e2a, cat2 + 64 * N2, gs2, Bn, H / 2, W / 2, ge2a, false, true, st));
-  chk(conv3_bwd(n, E2A, p1, e2a, ge2a, Bn, H / 2, W / 2, gp1, false, true, st));
+  bias_mask(gs2, cat2 + 64 * N2, g.bias(n, E2B), n->P[E2B].rows, N2, st);
+  chk(conv3_bwd(n, g, E2B, e2a, gs2, Bn, H / 2, W / 2, ge2a, st));
+  bias_mask(ge2a, e2a, g.bias(n, E2A), n->P[E2A].rows, N2, st);
+  chk(conv3_bwd(n, g, E2A, p1, ge2a, Bn, H / 2, W / 2, gp1, st));
   float* gs1 = gcat1 + 32 * N;
   pool_bwd(gp1, at<uint8_t>(n, p.arg1), gs1, 32 * Bn, H, W, true, st);
   float* e1a = at<float>(n, p.e1a);
   float* ge1a = at<float>(n, p.ge1a);
   float* a3 = at<float>(n, p.a3);
   float* ga3 = at<float>(n, p.ga3);
-  chk(conv3_bwd(n, E1B, e1a, cat1 + 32 * N, gs1, Bn, H, W, ge1a, false, true, st));
+  bias_mask(gs1, cat1 + 32 * N, g.bias(n, E1B), n->P[E1B].rows, N, st);
+  chk(conv3_bwd(n, g, E1B, e1a, gs1, Bn, H, W, ge1a, st));
   if (n->st) {   // the input needs no gradient
-    chk(conv3_bwd(n, E1A, at<float>(n, p.x0), e1a, ge1a, Bn, H, W, nullptr, false, true, st));
+    bias_mask(ge1a, e1a, g.bias(n, E1A), n->P[E1A].rows, N, st);
+    chk(conv3_bwd(n, g, E1A, at<float>(n, p.x0), ge1a, Bn, H, W, nullptr, st));
+    grad_reduce(g.t, at<float>(n, p.grad), st);
     chk(hipGetLastError());
     return e;
   }
-  chk(conv3_bwd(n, E1A, a3, e1a, ge1a, Bn, H, W, ga3, false, true, st));
+  bias_mask(ge1a, e1a, g.bias(n, E1A), n->P[E1A].rows, N, st);
+  chk(conv3_bwd(n, g, E1A, a3, ge1a, Bn, H, W, ga3, st));
   // temporal convolutions
   float* a2 = at<float>(n, p.a2);
   float* ga2 = at<float>(n, p.ga2);
-  relu_bwd(ga3, a3, 32 * N, st);
-  bias_grad(ga3, gb(n, T3), 32, N, st);
-  chk(gemm_dw(n, T3, ga3, a2, false, N, st));
+  bias_mask(ga3, a3, g.bias(n, T3), 32, N, st);
+  chk(lin_dw(n, g, T3, ga3, a2, N, st));
   chk(gemm_wtdy(n, T3, ga3, N, ga2, st));
   float* a1 = at<float>(n, p.a1);
   float* ga1 = at<float>(n, p.ga1);
-  uint16_t* col = at<uint16_t>(n, p.col);
   float* dcol = at<float>(n, p.dcol);
-  relu_bwd(ga2, a2, 32 * 5 * N, st);
-  bias_grad(ga2, gb(n, T2), 32, 5 * N, st);
-  im2col1(a1, col, 32, 10, 5, 5, 2, 2, N, st);
-  chk(gemm_dw(n, T2, ga2, col, true, 5 * N, st));
+  bias_mask(ga2, a2, g.bias(n, T2), 32, 5 * N, st);
+  chk(temporal_dw(n, g, T2, ga2, a1, 32, 10, 5, 2, 2, N, st));
   chk(gemm_wtdy(n, T2, ga2, 5 * N, dcol, st));
   col2im1(dcol, ga1, 32, 10, 5, 5, 2, 2, N, st);
-  relu_bwd(ga1, a1, 32 * 10 * N, st);
-  bias_grad(ga1, gb(n, T1), 32, 10 * N, st);
-  im2col1(at<float>(n, p.x0), col, 1, L, 10, 5, 5, 0, N, st);
-  chk(gemm_dw(n, T1, ga1, col, true, 10 * N, st));
+  bias_mask(ga1, a1, g.bias(n, T1), 32, 10 * N, st);
+  chk(temporal_dw(n, g, T1, ga1, at<float>(n, p.x0), 1, L, 10, 5, 0, N, st));
+  grad_reduce(g.t, at<float>(n, p.grad), st);
   chk(hipGetLastError());
   return e;
 }

@@ -107,8 +107,6 @@ void im2col1(const float* in, uint16_t* col, int C, int Tin, int Tout, int KT, i
 void col2im1(const float* dcol, float* din, int C, int Tin, int Tout, int KT, int S, int P, long long N,
              hipStream_t st);
 void bias_act(float* Y, const float* b, int C, long long N, bool relu, hipStream_t st);
-void relu_bwd(float* dY, const float* Y, long long n, hipStream_t st);
-void bias_grad(const float* dY, float* db, int C, long long N, hipStream_t st);
 void pool(const float* X, float* Y, uint8_t* arg, int CB, int H, int W, hipStream_t st);
 void pool_bwd(const float* dY, const uint8_t* arg, float* dX, int CB, int H, int W, bool acc, hipStream_t st);
 void up_scatter(const float* Z, const float* b, float* Y, int Co, int Bn, int h, int w, hipStream_t st);
@@ -117,6 +115,56 @@ void bce(const float* z, const float* y, float* dz, float* prob, float* part, lo
 void rmsprop(float* w, const float* g, float* v, uint16_t* wb, long long n, float lr, float rho, float eps,
              hipStream_t st);
 void to_bf16_copy(const float* w, uint16_t* wb, long long n, hipStream_t st);
+
+// ---- backward pass (k_nn_bwd.hip) ----
+// Weight gradients are sums over pixels K, formed in at most kGradSplits
+// ranges of grad_chunk(K) pixels whose partial sums grad_reduce adds in order.
+constexpr int kGradSplits = 32;
+int grad_chunk(long long K);
+int grad_ranges(long long K);
+// A weight gradient of partial sums P [Z][T][M][C], written to
+// grad[out + (m C + c) T + tap]; a bias gradient of C channels, written to
+// grad[out + c], from the chains of channels ch0 .. ch0 + C - 1 of bpart.
+struct GradSeg {
+  const float* P;
+  long long out;
+  int M, C, T, Z, block0;   // block0: first block of 256 elements
+};
+struct BiasSeg {
+  long long out;
+  int C, ch0;
+};
+struct GradTable {
+  GradSeg w[16];
+  BiasSeg b[16];
+  int nw, nb, wblocks;
+  const float* bpart;       // [channels][256]
+};
+void grad_reduce(const GradTable& t, float* grad, hipStream_t st);
+// dY [C][N] = 0 where not Y > 0 (Y may be null), and the 256 chains of each
+// channel's bias gradient into part [C][256]
+void bias_mask(float* dY, const float* Y, float* part, int C, long long N, hipStream_t st);
+// the same for dY[c][n] = wo[c] gl[n] (BF16 operands), the gradient that the
+// 1 x 1 output layer passes down
+void bias_outer(const float* gl, const uint16_t* wo, float* dY, const float* Y, float* part, int C, long long N,
+                hipStream_t st);
+// Partial weight gradients [grad_ranges][9][Co][Ci] of a 3 x 3 convolution
+// with input X [Ci][Bn][H][W]; false (nothing launched) unless W is a multiple
+// of 8, Co 32 or a multiple of 64 and the arrays are 16-byte aligned.
+bool dw3(const float* dY, const float* X, float* P, int Co, int Ci, int Bn, int H, int W, hipStream_t st);
+// Partial weight gradients [grad_ranges(K)][M][R] of dY [M][K] against the
+// temporal gather of X [C][Tin][Np] (row c KT + tap, column j Np + n:
+// X[c][j S + tap - Pd][n]), or against X [R][K] itself with Tin = KT = 1,
+// S = Pd = 0, Np = K; false unless Np and K are multiples of 8 and the arrays
+// are 16-byte aligned.
+bool dw1(const float* dY, const float* X, float* P, int M, int R, long long K, int Tin, int KT, int S, int Pd,
+         long long Np, hipStream_t st);
+// Input gradient of a 3 x 3 convolution, with Wd from reorder_dx (Ci a
+// multiple of 32); false (nothing launched) unless Co is 32, 64 or 128, Ci a
+// multiple of 32 and W 8, 16, 32, 64 or a larger multiple of 8.
+bool dx3(const uint16_t* Wd, const float* dY, float* dX, int Co, int Ci, int Bn, int H, int W, hipStream_t st,
+         hipError_t* err);
+void reorder_dx(const uint16_t* Wb, uint16_t* Wd, int Co, int Ci, hipStream_t st);
 
 // summary-image input (S, T): st [Bn][2][HW] -> x [2][Bn HW] with channel 0
 // the patch-standardised S and channel 1 T / sqrt(S + 25)
