@@ -10,8 +10,6 @@ namespace seg {
 
 constexpr int kPatch = 21;                 // tile side (Sec. II)
 constexpr int kPatchPix = kPatch * kPatch; // 441
-constexpr int kPatchK = 444;               // 441 padded to the MFMA depth 4
-constexpr int kMcFrames = 16;              // frames per workgroup (the MFMA's N)
 constexpr int kMcMaxRadius = 10;           // |dy|, |dx| <= R
 constexpr int kMcChunk = 2048;             // frames per scoring launch
 constexpr int kMcSlices = 8;               // patch slices per frame group

@@ -194,3 +194,26 @@ def test_benchmark_recording_full_size():
     _check_against_oracle(moved[sample], 8, got[sample], sc_s, out_s, tmpl)
     still = to_device_frames(video, DEV)
     assert torch.equal(out[:, 8:-8, 8:-8], still[:, 8:-8, 8:-8])
+
+
+@pytest.mark.parametrize("R,n", [(8, 16), (8, 340), (8, 512), (8, 2048), (10, 1100), (1, 33)])
+def test_every_split_of_the_vectors(R, n):
+    """Frame counts that give a workgroup 1 to 5 vector tiles per wave, on
+    frames of odd width over the whole 16-bit range, read from an address that
+    is no multiple of four: scores and corrected frames against the oracle
+    (the sums are exact integers, so the bars above hold as they are)."""
+    H, W = 2 * 21 + 2 * R + 1, 4 * 21 + 2 * R + 3   # 8 tiles, odd width and size
+    rng = np.random.default_rng(R * 10000 + n)
+    frames = rng.integers(0, 65536, size=(n + 1, H, W), dtype=np.uint16)
+    mc = MotionCorrector(H, W, DEV, radius=R)
+    d = to_device_frames(frames, DEV)
+    mc.set_template(d[:23])
+    motion, sc = mc.estimate(d[1:], scores=True)
+    out = mc.apply(d[1:], motion)
+    torch.cuda.synchronize()
+    tmpl = om.make_template(frames[:23])
+    assert np.array_equal(mc.template(), tmpl)
+    assert H * W % 2 == 1 and mc.n_patches == 8
+    idx = sorted({0, 1, 15, min(16, n - 1), n // 2, n - 2, n - 1})
+    _check_against_oracle(frames[1:], R, motion.cpu().numpy(), sc.cpu().numpy(), out.cpu().numpy().view(np.uint16),
+                          tmpl, frames_idx=idx)
