@@ -85,6 +85,18 @@ __device__ __forceinline__ double gram_wave(const double* X, int len, int lane, 
     const int span = (len + QG - 1) / QG, j1 = min(len, (q + 1) * span);
     double g0 = 0.0, g1 = 0.0;
     int j = q * span;
+    for (; j + 3 < j1; j += 4) {
+      double x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        x[u] = X[(j + u) * R8 + n1];
+        y[u] = X[(j + u) * R8 + n2];
+      }
+      g0 = fma(x[0], y[0], g0);
+      g1 = fma(x[1], y[1], g1);
+      g0 = fma(x[2], y[2], g0);
+      g1 = fma(x[3], y[3], g1);
+    }
     for (; j + 1 < j1; j += 2) {
       g0 = fma(X[j * R8 + n1], X[j * R8 + n2], g0);
       g1 = fma(X[(j + 1) * R8 + n1], X[(j + 1) * R8 + n2], g1);
@@ -170,43 +182,6 @@ __device__ __forceinline__ u64 get_word(u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The same word read through this XCD's L2 (workgroup scope: past the L1,
-// not past the L2). The planner places a component's workgroups on one XCD
-// where it can, so a slot written there (the agent-scope store passes
-// through that L2) is seen at L2 latency; a word written on another XCD may
-// sit stale in this L2, so the waits below also read with agent scope every
-// fourth poll. The tags make a stale word harmless: it is only waited on.
-__device__ __forceinline__ u64 get_word_near(u64* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ bool tagged(u64 w, unsigned tag) { return (unsigned)(w >> 32) == tag; }
-
-// Waits until both halves at p and p + xs carry `tag` and returns them;
-// ok is false when the component was abandoned or the wall-clock limit
-// passed (then it marks the component abandoned and sets the error flag).
-struct Halves {
-  u64 hi, lo;
-  bool ok;
-};
-__device__ __forceinline__ Halves wait_words(u64* p, int xs, unsigned tag, unsigned* abandoned,
-                                             unsigned* error, long long limit) {
-  const long long t0 = wall_clock64();
-  for (unsigned n = 0;; ++n) {
-    __builtin_amdgcn_s_sleep(2);
-    const bool far = (n & 3) == 3;
-    const u64 hi = far ? get_word(p) : get_word_near(p), lo = far ? get_word(p + xs) : get_word_near(p + xs);
-    if (tagged(hi, tag) && tagged(lo, tag)) return {hi, lo, true};
-    if ((n & 15) == 15 && __hip_atomic_load(abandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
-      return {0, 0, false};
-    if (wall_clock64() - t0 > limit) {
-      __hip_atomic_store(abandoned, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return {0, 0, false};
-    }
-  }
-}
-
 __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
   extern __shared__ double dyn[];
   __shared__ double red[CW];
@@ -233,55 +208,82 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
   unsigned ex = 0;  // exchanges done
   bool dead = false;  // this thread gave up waiting (the workgroup leaves at the next check)
   if (t == 0) bad = 0;
-  // slot of workgroup w for exchange e: XS high words, then XS low words
-  auto slot = [&](int w, unsigned e) { return s.xbuf + ((size_t)(w0 + w) * 2 + (e & 1)) * 2 * XS; };
+  // a component of one workgroup exchanges nothing: what it would put in its
+  // slot goes to the LDS words where the totals are wanted (the caller's
+  // barriers, or the thread itself, order the accesses)
+  const bool alone = nw == 1;
   // element j of this workgroup's slot for exchange e
   auto put = [&](unsigned e, size_t j, double v) {
-    u64* p = slot(r, e) + j;
+    if (alone) {
+      if (j < (size_t)R8 * K) FtP[j] = v;
+      else gF[j - (size_t)R8 * K] = v;
+      return;
+    }
+    u64* p = s.xbuf + (((unsigned)(w0 + r) * 2 + (e & 1)) * 2 * (unsigned)XS + (unsigned)j);
     const u64 b = (u64)__double_as_longlong(v);
     put_word(p, e + 1, (unsigned)(b >> 32));
     put_word(p + XS, e + 1, (unsigned)b);
   };
   // sum (or max) of element j over the component's slots of exchange e, in
-  // slot order, waiting for each slot's words; twelve slots per round of
-  // memory latency
-  auto gather = [&](size_t j, unsigned e, bool take_max) {
+  // slot order, waiting until each slot's words carry its tag. Up to eight
+  // slots are polled together, so that what is late at the first look costs
+  // one more round trip for all of them; each late slot polled by itself, with
+  // three of four polls at workgroup scope (which the L1 answers from what it
+  // read before), made a sweep of 256 x 256 x 3,000 take 16 us instead of 8.
+  auto poll = [&](auto count, int wb, unsigned j, unsigned e, bool take_max, double& v) {
+    constexpr int C = decltype(count)::value;
     const unsigned tag = e + 1;
-    double v = 0.0;
-    if (dead) return v;
-    for (int wb = 0; wb < nw; wb += 12) {
-      u64 hi[12], lw[12];
-      // all 24 loads go out before the first use (slots past the last are
-      // read as the last one and not used)
+    u64 hi[C], lw[C];
+    const long long t0 = wall_clock64();
+    for (unsigned n = 0;; ++n) {
+      // all loads go out before the first use (slots past the last are read
+      // as the last one and not used)
 #pragma unroll
-      for (int q = 0; q < 12; ++q) {
-        u64* p = slot(min(wb + q, nw - 1), e) + j;
-        hi[q] = get_word_near(p);
-        lw[q] = get_word_near(p + XS);
+      for (int q = 0; q < C; ++q) {
+        // 32-bit offsets from one base: two addresses per slot held in
+        // scalar registers spilled hundreds of them
+        const unsigned at = ((unsigned)(w0 + min(wb + q, nw - 1)) * 2 + (e & 1)) * 2 * (unsigned)XS + j;
+        hi[q] = get_word(s.xbuf + at);
+        lw[q] = get_word(s.xbuf + (at + (unsigned)XS));
       }
-      asm volatile("" : "+v"(hi[0]), "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]), "+v"(hi[4]), "+v"(hi[5]),
-                        "+v"(hi[6]), "+v"(hi[7]), "+v"(hi[8]), "+v"(hi[9]), "+v"(hi[10]), "+v"(hi[11]),
-                        "+v"(lw[0]), "+v"(lw[1]), "+v"(lw[2]), "+v"(lw[3]), "+v"(lw[4]), "+v"(lw[5]),
-                        "+v"(lw[6]), "+v"(lw[7]), "+v"(lw[8]), "+v"(lw[9]), "+v"(lw[10]), "+v"(lw[11]));
 #pragma unroll
-      for (int q = 0; q < 12; ++q)
-        if (wb + q < nw) {
-          if (!tagged(hi[q], tag) || !tagged(lw[q], tag)) {
-            const Halves h = dead ? Halves{0, 0, false}
-                                  : wait_words(slot(wb + q, e) + j, XS, tag, abandoned, error, s.limit);
-            if (!h.ok) {
-              dead = true;
-              bad = 1;
-              return 0.0;
-            }
-            hi[q] = h.hi;
-            lw[q] = h.lo;
-          }
-          const double x = __longlong_as_double((long long)((hi[q] << 32) | (lw[q] & 0xffffffffull)));
-          v = take_max ? fmax(v, x) : v + x;
-        }
+      for (int q = 0; q < C; ++q) asm volatile("" : "+v"(hi[q]), "+v"(lw[q]));
+      unsigned late = 0;
+#pragma unroll
+      for (int q = 0; q < C; ++q) late |= ((unsigned)(hi[q] >> 32) ^ tag) | ((unsigned)(lw[q] >> 32) ^ tag);
+      if (late == 0) break;
+      if ((n & 15) == 15 && __hip_atomic_load(abandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
+        dead = true;
+      } else if (wall_clock64() - t0 > s.limit) {   // no slot comes this late: give the component up
+        __hip_atomic_store(abandoned, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        dead = true;
+      }
+      if (dead) {
+        bad = 1;
+        return;
+      }
     }
-    return v;
+#pragma unroll
+    for (int q = 0; q < C; ++q)
+      if (wb + q < nw) {
+        const double x = __longlong_as_double((long long)((hi[q] << 32) | (lw[q] & 0xffffffffull)));
+        v = take_max ? fmax(v, x) : v + x;
+      }
+  };
+  auto gather = [&](unsigned j, unsigned e, bool take_max) {
+    if (alone) return j < (unsigned)(R8 * K) ? FtP[j] : gF[j - (unsigned)(R8 * K)];
+    double v = 0.0;
+    for (int wb = 0; wb < nw && !dead;) {
+      if (nw - wb > 4) {
+        poll(std::integral_constant<int, 8>{}, wb, j, e, take_max, v);
+        wb += 8;
+      } else {
+        poll(std::integral_constant<int, 4>{}, wb, j, e, take_max, v);
+        wb += 4;
+      }
+    }
+    return dead ? 0.0 : v;
   };
   __syncthreads();
 // leave when any thread of the workgroup gave up waiting (read after a barrier)
@@ -384,6 +386,7 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
       mx = block_max(mx, red);
       if (t == 0) put(ex, n, mx);
     }
+    if (alone) __syncthreads();
     for (int m = t; m < ml; m += CT)
       for (int n = 0; n < R8; ++n) {
         double v = 0.0;
@@ -410,7 +413,8 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
         // Wave 15: F^T F, whole within the wave (gram_wave), straight to the
         // slot.
         {
-          const int QC = max(1, min(min(CV / K, 8), s.scr / (K * NR)));
+          // chunks of about 16 rows, at least 8 and at most 24 of them
+          const int QC = max(1, min(min(CV / K, max(8, min(24, ml / 16))), s.scr / (K * NR)));
           const int rows = (ml + QC - 1) / QC;
           if (t < CV) {
             for (int e = t; e < QC * K; e += CV) {
@@ -420,6 +424,24 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
 #pragma unroll
               for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
               int m = q * rows;
+              if constexpr (NR <= 3) {   // four rows' reads in flight
+                for (; m + 3 < m1; m += 4) {
+                  double p[4], f[4][NR];
+#pragma unroll
+                  for (int u = 0; u < 4; ++u) {
+                    p[u] = (double)Pl[(m + u) * Kp + i];
+#pragma unroll
+                    for (int n = 0; n < NR; ++n) f[u][n] = F[(m + u) * R8 + n];
+                  }
+#pragma unroll
+                  for (int n = 0; n < NR; ++n) {
+                    s0[n] = fma(f[0][n], p[0], s0[n]);
+                    s1[n] = fma(f[1][n], p[1], s1[n]);
+                    s0[n] = fma(f[2][n], p[2], s0[n]);
+                    s1[n] = fma(f[3][n], p[3], s1[n]);
+                  }
+                }
+              }
               for (; m + 1 < m1; m += 2) {
                 const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[(m + 1) * Kp + i];
 #pragma unroll
@@ -458,11 +480,11 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
         // the NR K entries of F^T P, then the upper triangle of F^T F (mirrored)
         for (int e = t; e < NR * K + NP; e += CT) {
           if (e < NR * K) {
-            FtP[e] = gather(e, ex, false);
+            if (!alone) FtP[e] = gather(e, ex, false);
           } else {
             int n1, n2;
             pair_of<NR>(e - NR * K, n1, n2);
-            const double v = gather((size_t)R8 * K + n1 * R8 + n2, ex, false);
+            const double v = gather((unsigned)(R8 * K + n1 * R8 + n2), ex, false);
             gF[n1 * R8 + n2] = v;
             gF[n2 * R8 + n1] = v;
           }
@@ -582,6 +604,7 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
       if (t == 0) put(ex, n, mx);
     }
     double* peak = scr;
+    if (alone) __syncthreads();
     if (t < N) peak[t] = gather(t, ex, true);
     ++ex;
     LEAVE_IF_ABANDONED();
@@ -634,12 +657,16 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
   // exchange slots: two per workgroup of the largest launch, in xbuf, each
   // of XS high and XS low words
   const size_t slot_bytes = (size_t)2 * 2 * XS * 8;
-  // Slice widths in order of preference (measured: 96 rows balance the
-  // per-sweep exchange against the per-workgroup work; at most twelve
-  // 16-row tiles). Components are packed, in order, into launches of at most
-  // one workgroup per compute unit; each launch costs about the same (its
-  // sweeps are latency bound), so the width with the fewest launches wins.
-  const int widths[] = {96, 128, 160, 192, 64, 32};
+  // Slice widths in order of preference: 96 rows balance the per-sweep exchange
+  // against the per-workgroup work where there are many segments, 160 where
+  // there are few and a row is little work (at 60 segments 1.64 ms against
+  // 1.86 for 96 rows and 1.81 for 208; at 90 2.34 against 2.39; at 120 1.79
+  // against 1.54). At most twelve 16-row tiles. Components are packed, in
+  // order, into launches of at most one workgroup per compute unit; each
+  // launch costs about the same (its sweeps are latency bound), so the width
+  // with the fewest launches wins.
+  const bool few = K <= 96;
+  const int widths[] = {few ? 160 : 96, 128, few ? 96 : 160, 192, 64, 32};
   int best_mw = 0, best_groups = 0;
   for (const int mw : widths) {
     int scr = 0;

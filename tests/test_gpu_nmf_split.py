@@ -131,3 +131,38 @@ def test_split_over_several_launches():
     assert np.array_equal(fs["component"], f1["component"])
     assert np.array_equal(fs["masks"], f1["masks"])
     assert np.abs(fs["weights"] - f1["weights"]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("K", [3, 96, 97])
+def test_component_sizes_of_every_exchange(K):
+    """Components of one slice (which exchange nothing), of a few and of more
+    than eight (polled in two rounds), on both sides of the segment count where
+    the slice width changes: both paths, which differ in the order of FP64 sums
+    only, to the bars of the comparison above."""
+    rng = np.random.default_rng(K)
+    H, W = 96, 192
+    yy, xx = np.mgrid[0:H, 0:W]
+    T = rng.uniform(0.5, 1.5, (K, H, W)).astype(np.float32)
+    discs = [(12, 12, 5), (14, 40, 9), (40, 24, 14), (46, 100, 20), (46, 112, 20), (30, 160, 16), (66, 160, 16)]
+    for j, (cy, cx, r) in enumerate(discs):
+        d2 = (yy - cy) ** 2 + (xx - cx) ** 2
+        on = rng.random(K) < 0.4
+        on[j % K] = True
+        for i in np.flatnonzero(on):
+            T[i] += np.where(d2 <= r * r, rng.uniform(8, 14) * (1.3 - d2 / (r * r + 1.0)), 0.0).astype(np.float32)
+    D = np.full((K, H, W), 1.0 / np.sqrt(2 * np.pi), np.float32)
+    got = []
+    for path in (abi.SEG_NMF_SINGLE, abi.SEG_NMF_SPLIT):
+        s = Session(H, W, 50 * K, nmf_path=path, min_event_segs=1, area_max=4000)
+        s.load_summaries(T, np.ones_like(T), D)
+        s.finalize()
+        torch.cuda.synchronize()
+        assert s.profile()["nmf_path"] == path
+        got.append(s.footprints())
+        s.close()
+    one, two = got
+    assert len(one["component"]) >= 5
+    assert np.array_equal(one["component"], two["component"])
+    assert np.array_equal(one["masks"], two["masks"])
+    assert np.abs(one["weights"] - two["weights"]).max() <= 1e-5
+    assert np.abs(one["activity"] - two["activity"]).max() <= 1e-5 * np.abs(one["activity"]).max()
