@@ -137,22 +137,11 @@ __global__ __launch_bounds__(256) void k_gemm(const TA* __restrict__ A, long lon
 //             for the transposed 2 x 2 convolution: row 4 co + 2 a + e of the
 //             product, plus bias[co], is stored to C at channel co, pixel
 //             (2 y + a, 2 x + e) of an image of 2 H x 2 W (X's pixels H x W),
-//             so the product lands directly in the concatenation buffer;
-//   GV_TCONV  the 1-D temporal im2col of BF16 X [C][Tin][Np]: row
-//             k = c KT + tap, column j Np + n holds
-//             X[c][j S + tap - P][n] (zero outside 0 .. Tin - 1), what
-//             im2col1 would write, gathered as it is loaded (Np a multiple
-//             of 8, so a group of 8 columns lies in one j); C is stored as
-//             FP32, or as BF16 bits when `out_h` (row-major when 1; when 2,
-//             with rows as channels in blocks of 16, see cblk).
-enum { GV_BF16 = 0, GV_IM2COL = 1, GV_UP = 2, GV_TCONV = 3 };
+//             so the product lands directly in the concatenation buffer.
+enum { GV_BF16 = 0, GV_IM2COL = 1, GV_UP = 2 };
 struct Im2col {
   const float* X;
   int Bn, H, W;
-  // GV_TCONV
-  const void* TX;
-  int Tin, KT, S, P, out_h, xcd;
-  long long Np;
 };
 // bias (may be null) and relu are applied to the stored values (not with
 // accumulate), as bias_act does after an unfused product.
@@ -168,18 +157,7 @@ __global__ __launch_bounds__(256) void k_gemm_v(const uint16_t* __restrict__ A, 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wm = MT == 64 ? wv >> 1 : 0, wn = MT == 64 ? wv & 1 : wv;
   const int m0 = blockIdx.y * MT;
-  int n0 = blockIdx.x * NT;
-  if constexpr (MODE == GV_TCONV) {
-    if (ic.xcd) {
-      // The output samples j of one pixel range read overlapping input rows:
-      // tile t = (pixel range, j) with j fastest, and the workgroups that the
-      // dispatcher sends to one XCD (blockIdx.x mod 8) take one contiguous
-      // run of tiles, so the re-reads hit that XCD's L2.
-      const int T = gridDim.x, x = blockIdx.x, t = (x & 7) * (T >> 3) + (x >> 3);
-      const int tout = (int)(N / ic.Np), j = t % tout;
-      n0 = (int)(j * ic.Np) + (t / tout) * NT;
-    }
-  }
+  const int n0 = blockIdx.x * NT;
   // A: thread -> (row am, k group ak); B: thread -> (k row bk, n group bn + 64 j)
   const int am = tid >> 2, ak = (tid & 3) * 8;
   const bool a_on = am < MT;
@@ -189,16 +167,6 @@ __global__ __launch_bounds__(256) void k_gemm_v(const uint16_t* __restrict__ A, 
   // column are found once
   int py[NB], px[NB];
   long long poff[NB];
-  if constexpr (MODE == GV_TCONV) {
-    // a thread's column groups are fixed: sample j and pixel n found once
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int gn = n0 + bn + 64 * j;
-      const long long jj = gn / ic.Np;
-      py[j] = gn < N ? (int)jj * ic.S - ic.P : -(1 << 20);   // input sample of tap 0 (off-range groups load nothing)
-      poff[j] = gn - jj * ic.Np;
-    }
-  }
   if constexpr (MODE == GV_IM2COL) {
     const int HW = ic.H * ic.W;
 #pragma unroll
@@ -212,15 +180,7 @@ __global__ __launch_bounds__(256) void k_gemm_v(const uint16_t* __restrict__ A, 
   }
   auto load = [&](int k0) {
     const int gm = m0 + am, gk = k0 + ak;
-    if (MODE == GV_TCONV && (sam & 7)) {   // rows not 16-byte aligned (K of 5): element loads
-      uint16_t v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = (a_on && gm < M && gk + q < K) ? A[gm * sam + gk + q] : (uint16_t)0;
-      ra = make_uint4(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16), v[4] | ((uint32_t)v[5] << 16),
-                      v[6] | ((uint32_t)v[7] << 16));
-    } else {
-      ra = (a_on && gm < M && gk < K) ? *reinterpret_cast<const uint4*>(A + gm * sam + gk) : make_uint4(0, 0, 0, 0);
-    }
+    ra = (a_on && gm < M && gk < K) ? *reinterpret_cast<const uint4*>(A + gm * sam + gk) : make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int gkb = k0 + bk, gn = n0 + bn + 64 * j;
@@ -233,18 +193,6 @@ __global__ __launch_bounds__(256) void k_gemm_v(const uint16_t* __restrict__ A, 
           const float4 lo = src[0], hi = src[1];
           v = make_uint4(to_bf16(lo.x) | ((uint32_t)to_bf16(lo.y) << 16), to_bf16(lo.z) | ((uint32_t)to_bf16(lo.w) << 16),
                          to_bf16(hi.x) | ((uint32_t)to_bf16(hi.y) << 16), to_bf16(hi.z) | ((uint32_t)to_bf16(hi.w) << 16));
-        }
-        rb[j] = v;
-      } else if constexpr (MODE == GV_TCONV) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        (void)gn;
-        if (gkb < K) {
-          const int c = gkb / ic.KT, tap = gkb - c * ic.KT;
-          const int t = py[j] + tap;
-          if (t >= 0 && t < ic.Tin) {
-            const long long off = ((long long)c * ic.Tin + t) * ic.Np + poff[j];
-            v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(ic.TX) + off);
-          }
         }
         rb[j] = v;
       } else {
@@ -298,51 +246,6 @@ __global__ __launch_bounds__(256) void k_gemm_v(const uint16_t* __restrict__ A, 
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
     }
     __syncthreads();
-  }
-  if constexpr (MODE == GV_TCONV) {
-    if (ic.out_h) {
-      // BF16 output: the tile goes through LDS so that each thread stores
-      // 16 bytes of one row (8 columns; N is a multiple of 8)
-      __shared__ __attribute__((aligned(16))) uint16_t Ts[MT][NT + 8];
-      const int cl = wn * 32 + (lane & 31);
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rl = wm * 32 + 8 * g + 4 * (lane >> 5) + r, row = m0 + rl;
-          float v = acc[4 * g + r];
-          if (bias && row < M) {
-            v += bias[row];
-            if (relu) v = fmaxf(v, 0.f);
-          }
-          Ts[rl][cl] = to_bf16(v);
-        }
-      __syncthreads();
-      if (ic.out_h == 2) {
-        // channel blocks of 16 (M a multiple of 16, rows = channels, columns
-        // = pixels): a thread gathers the 16 channels of one pixel from the
-        // tile's column and stores them as 32 bytes
-        for (int e = tid; e < (MT / 16) * NT; e += 256) {
-          const int cb = e / NT, cl2 = e - cb * NT, gc = n0 + cl2, c0 = m0 + 16 * cb;
-          uint32_t w[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) w[k] = Ts[16 * cb + 2 * k][cl2] | ((uint32_t)Ts[16 * cb + 2 * k + 1][cl2] << 16);
-          if (c0 < M && gc < N) {
-            uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(C) + cblk(c0, gc, N));
-            dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-            dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
-          }
-        }
-        return;
-      }
-      for (int e = tid; e < MT * (NT / 8); e += 256) {
-        const int rl = e / (NT / 8), c8 = (e - rl * (NT / 8)) * 8, row = m0 + rl, gc = n0 + c8;
-        if (row < M && gc < N)
-          *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(C) + (long long)row * ldc + gc) =
-              *reinterpret_cast<const uint4*>(&Ts[rl][c8]);
-      }
-      return;
-    }
   }
   const int col = n0 + wn * 32 + (lane & 31);
   if (col >= N) return;
@@ -1275,86 +1178,193 @@ __global__ void k_tnorm(const uint16_t* __restrict__ frames, float* __restrict__
   for (int t = 0; t < L; ++t) out[((long long)t * Bn + b) * HW + p] = ((float)f[(long long)t * HW] - mean) * inv;
 }
 
-// The frame normalisation and the first temporal convolution (one input
-// channel, 32 outputs, kernel 5, stride 5, no padding: 50 -> 10 samples) in
-// one pass, for inference. A wave takes 64 pixels. Each lane loads its
-// pixel's 50 frames and normalises them as k_tnorm does (sequential FP32 sum,
-// mean, 1 / sqrt(mean + 25)), rounding to BF16 as im2col1 does; for output
-// sample j the 5 values are the depth of one 32 x 32 x 16 MFMA, lanes
-// 32..63 handing their pixels to lanes 0..31 for a second one, each followed
-// by the all-zero step that the product kernels run for the rest of their
-// 32-deep chunk, so the sums are those of im2col1 + gemm. Bias, ReLU and BF16
-// rounding as bias_act and the BF16 store; a1 [32][10][Np] (row c, column
-// j Np + n) is written through a per-wave LDS tile, 16 bytes per lane.
-constexpr int T1_L = 50, T1_K = 5, T1_TO = 10;
-__global__ __launch_bounds__(256) void k_tconv1_h(const uint16_t* __restrict__ frames, const uint16_t* __restrict__ Wb,
-                                                  const float* __restrict__ bias, uint16_t* __restrict__ a1, int Bn,
-                                                  long long HW) {
-  __shared__ __attribute__((aligned(16))) uint16_t Ts[4][32][64 + 8];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5;
-  const long long Np = (long long)Bn * HW;
-  const long long p0 = ((long long)blockIdx.x * 4 + wv) * 64;   // the wave's first pixel (Np % 64 == 0)
-  if (p0 >= Np) return;   // whole waves; no workgroup barrier below
-  const long long n = p0 + lane;
-  const long long b = n / HW, p = n - b * HW;
-  const uint16_t* f = frames + b * T1_L * HW + p;
-  float v[T1_L];
+// The temporal layers in one pass: frame normalisation, 50 -> 10 samples (one
+// input channel, 32 outputs, kernel 5, stride 5), 10 -> 5 (32 channels, kernel
+// 5, stride 2, padding 2), 5 -> 1 (kernel 5), each with bias and ReLU. Between
+// the layers an activation is 320, 160 and 32 values per pixel; nothing but the
+// frames is read and nothing but the last one written (training keeps them all,
+// in FP32), so what bounds it is its own arithmetic: 70 products of 32 x 32 x 16
+// per 32 pixels, and the rounding and packing between them.
+//
+// A wave takes 64 pixels, 32 at a time. Each lane normalises one pixel's frames
+// as k_tnorm does (sequential FP32 sum, mean, 1 / sqrt(mean + 25)). The rows of
+// every product are its output channels, ordered so that lane (h, pixel) gets
+// channels 16 h .. 16 h + 15; the depth of the second and third product is
+// k = 5 c + tap, 16 per step, so the sums are those of im2col1 + gemm. A lane's
+// 16 channels are 80 consecutive values of that depth: for output sample j it
+// puts them, as 40 words, in the wave's LDS tile [pixel][80 words], from which
+// the operands (8 values) are 16-byte reads. Rows of 84 words keep both free of
+// bank conflicts, and only the wave itself reads what it wrote: no barrier.
+//
+// Eight segments of 256 x 256 take 100 us; a kernel per layer, gathering its
+// im2col from BF16 activations in HBM, took 390. In training, sixteen of
+// 64 x 64 with every activation stored in FP32 take 44 us; normalisation,
+// im2col matrices, products and bias passes took 325. Two waves per SIMD with
+// both weight operands in LDS beat one with the second layer's in registers
+// (348 against 360 us for the whole inference call).
+constexpr int T_L = 50, T_KT = 5, T_J1 = 10, T_J2 = 5, T_C = 32, T_K = T_C * T_KT;
+constexpr int kTemporalGrid = 512;   // two workgroups per compute unit, each over many pixels (256 to 2,048: within 4 %)
+constexpr int T_PS = 84;   // words per pixel of the operand tile
+struct Temporal {
+  const uint16_t* frames;                  // [Bn][50][HW]
+  const uint16_t *w1, *w2, *w3;            // [32][5], [32][160], [32][160]
+  const float *b1, *b2, *b3;
+  uint16_t* a3h;                           // inference: last activation, channel blocks
+  float *x0, *a1, *a2, *a3;                // training: normalised frames and activations, planar
+  int Bn;
+  long long HW;
+};
+
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  bf16x2 v;
+  v[0] = (__bf16)a;
+  v[1] = (__bf16)b;
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+template <bool TRAIN>
+__global__ __launch_bounds__(256, 2) void k_temporal(Temporal q) {
+  __shared__ uint4 W2s[10 * 64], W3s[10 * 64];
+  __shared__ float bs[3][T_C];
+  __shared__ __attribute__((aligned(16))) uint32_t Ss[4][32 * T_PS];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, px = lane & 31;
+  const long long Np = (long long)q.Bn * q.HW;
+  // output channel of this lane's operand row: row 8 (i / 4) + 4 h + i % 4 of
+  // the result is register i of half h
+  const int row = 16 * ((px >> 2) & 1) + 4 * (px >> 3) + (px & 3);
+  bf16x8 a;   // first layer: depth 0..4 in lanes 0..31, zero elsewhere
 #pragma unroll
-  for (int t = 0; t < T1_L; ++t) v[t] = (float)f[(long long)t * HW];
-  float s = 0.f;
-#pragma unroll
-  for (int t = 0; t < T1_L; ++t) s += v[t];
-  const float mean = s / T1_L;
-  const float inv = rsqrtf(mean + 25.f);
-  // weights: row lane & 31, depth 0..4 in lanes 0..31, zero elsewhere
-  bf16x8 a, z;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    a[q] = __builtin_bit_cast(__bf16, (h == 0 && q < T1_K) ? Wb[(lane & 31) * T1_K + q] : (uint16_t)0);
-    z[q] = __builtin_bit_cast(__bf16, (uint16_t)0);
+  for (int k = 0; k < 8; ++k) a[k] = __builtin_bit_cast(__bf16, (h == 0 && k < T_KT) ? q.w1[row * T_KT + k] : (uint16_t)0);
+  for (int e = tid; e < 10 * 64; e += 256) {
+    const int r = e & 31, ch = 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+    W2s[e] = *reinterpret_cast<const uint4*>(q.w2 + ch * T_K + 16 * (e >> 6) + 8 * ((e >> 5) & 1));
+    W3s[e] = *reinterpret_cast<const uint4*>(q.w3 + ch * T_K + 16 * (e >> 6) + 8 * ((e >> 5) & 1));
   }
-  float bv[16];
+  if (tid < T_C) {
+    bs[0][tid] = q.b1[tid];
+    bs[1][tid] = q.b2[tid];
+    bs[2][tid] = q.b3[tid];
+  }
+  __syncthreads();
+  uint32_t* mine = Ss[wv] + px * T_PS;
+  // the words of this lane's channels into the tile, and the operands of one
+  // depth step back; a wave's LDS accesses keep their order
+  auto put = [&](const uint32_t (&d)[40]) {
+    asm volatile("" ::: "memory");
 #pragma unroll
-  for (int k = 0; k < 16; ++k) bv[k] = bias[8 * (k >> 2) + 4 * h + (k & 3)];
+    for (int m = 0; m < 10; ++m)
+      *reinterpret_cast<uint4*>(mine + 40 * h + 4 * m) = make_uint4(d[4 * m], d[4 * m + 1], d[4 * m + 2], d[4 * m + 3]);
+    asm volatile("" ::: "memory");
+  };
+  auto get = [&](int g) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(mine + 8 * g + 4 * h)); };
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto act = [&](const f32x16& c, int layer, int i) { return fmaxf(c[i] + bs[layer][16 * h + i], 0.f); };
+
+  for (long long p0 = ((long long)blockIdx.x * 4 + wv) * 64; p0 < Np; p0 += (long long)gridDim.x * 256) {
+    uint32_t w[T_J1][3];   // the normalised frames of this lane's pixel, five per output sample
+    {
+      const long long n = p0 + lane, b = n / q.HW;
+      const uint16_t* f = q.frames + b * T_L * q.HW + (n - b * q.HW);
+      float v[T_L];
 #pragma unroll
-  for (int j = 0; j < T1_TO; ++j) {
-    uint32_t w[3];
+      for (int t = 0; t < T_L; ++t) v[t] = (float)f[(long long)t * q.HW];
+      float s = 0.f;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const uint16_t lo = to_bf16((v[5 * j + 2 * q] - mean) * inv);
-      const uint16_t hi = 2 * q + 1 < T1_K ? to_bf16((v[5 * j + 2 * q + 1] - mean) * inv) : (uint16_t)0;
-      w[q] = lo | ((uint32_t)hi << 16);
-    }
-    uint32_t u[3];   // lanes 0..31: the words of lane + 32 (pixels 32..63)
+      for (int t = 0; t < T_L; ++t) s += v[t];
+      const float mean = s / T_L;
+      const float inv = rsqrtf(mean + 25.f);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) u[q] = from_upper_half(w[q]);
-    f32x16 acc[2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      const uint32_t* src = blk ? u : w;
-      const uint4 bq = h == 0 ? make_uint4(src[0], src[1], src[2], 0) : make_uint4(0, 0, 0, 0);
-      f32x16 c;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) c[i] = 0.f;
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, bq), c, 0, 0, 0);
-      acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(z, z, c, 0, 0, 0);
-    }
-    // tile [32 channels][64 pixels] of sample j, then 16-byte row pieces
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const float y = fmaxf(acc[blk][k] + bv[k], 0.f);
-        Ts[wv][8 * (k >> 2) + 4 * h + (k & 3)][32 * blk + (lane & 31)] = to_bf16(y);
+      for (int t = 0; t < T_L; ++t) {
+        v[t] = (v[t] - mean) * inv;
+        if constexpr (TRAIN) q.x0[(long long)t * Np + n] = v[t];
       }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = lane + 64 * i, row = e >> 3, c8 = (e & 7) * 8;
-      *reinterpret_cast<uint4*>(a1 + (long long)row * T1_TO * Np + (long long)j * Np + p0 + c8) =
-          *reinterpret_cast<const uint4*>(&Ts[wv][row][c8]);
+      for (int j = 0; j < T_J1; ++j) {
+        w[j][0] = pk_bf16(v[5 * j], v[5 * j + 1]);
+        w[j][1] = pk_bf16(v[5 * j + 2], v[5 * j + 3]);
+        w[j][2] = pk_bf16(v[5 * j + 4], 0.f);
+      }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 1
+    for (int blk = 0; blk < 2; ++blk) {
+      const long long n = p0 + 32 * blk + px;
+      // training: a row's channel of half 0, `per` rows to a channel
+      auto store = [&](float* o, uint32_t per, float y) {
+        *reinterpret_cast<float*>(reinterpret_cast<char*>(o) + 4u * (16u * h * per * (uint32_t)Np + 32u * blk + px)) = y;
+      };
+      uint32_t P[T_J1 / 2][16];   // first activation: samples 2 s and 2 s + 1 of channel 16 h + i
+#pragma unroll
+      for (int s = 0; s < T_J1 / 2; ++s) {
+        f32x16 c[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          // lanes 32..63 hold finite values that meet zeros
+          const uint4 bq = make_uint4(w[2 * s + k][0], w[2 * s + k][1], w[2 * s + k][2], 0);
+          c[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, bq), zero, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float y0 = act(c[0], 0, i), y1 = act(c[1], 0, i);
+          P[s][i] = pk_bf16(y0, y1);
+          if constexpr (TRAIN) {
+            store(q.a1 + ((long long)i * T_J1 + 2 * s) * Np + p0, 10, y0);
+            store(q.a1 + ((long long)i * T_J1 + 2 * s + 1) * Np + p0, 10, y1);
+          }
+        }
+      }
+      uint32_t D[40];   // second activation: value 5 i + j of this lane's 80
+#pragma unroll
+      for (int m = 0; m < 40; ++m) D[m] = 0;
+#pragma unroll
+      for (int j = 0; j < T_J2; ++j) {
+        uint32_t d[40];   // taps 0..4 of output sample j: samples 2 j - 2 .. 2 j + 2, zero outside
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          auto word = [&](int i, int s) { return s < 0 || s >= T_J1 / 2 ? 0u : P[s][2 * m + i]; };
+          d[5 * m] = word(0, j - 1);
+          d[5 * m + 1] = word(0, j);
+          d[5 * m + 2] = (word(0, j + 1) & 0xffffu) | (word(1, j - 1) << 16);
+          d[5 * m + 3] = (word(1, j - 1) >> 16) | (word(1, j) << 16);
+          d[5 * m + 4] = (word(1, j) >> 16) | (word(1, j + 1) << 16);
+        }
+        put(d);
+        f32x16 c = zero;
+#pragma unroll
+        for (int g = 0; g < 10; ++g) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, W2s[64 * g + lane]), get(g), c, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float y = act(c, 1, i);
+          if constexpr (TRAIN) store(q.a2 + ((long long)i * T_J2 + j) * Np + p0, 5, y);
+          const int e = 5 * i + j;
+          D[e >> 1] |= pk_bf16(e & 1 ? 0.f : y, e & 1 ? y : 0.f);
+        }
+      }
+      put(D);
+      f32x16 c = zero;
+#pragma unroll
+      for (int g = 0; g < 10; ++g)
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, W3s[64 * g + lane]), get(g), c, 0, 0, 0);
+      float y[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) y[i] = act(c, 2, i);
+      if constexpr (TRAIN) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) store(q.a3 + (long long)i * Np + p0, 1, y[i]);
+      } else {
+        uint4* o = reinterpret_cast<uint4*>(q.a3h + cblk(16 * h, n, Np));
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          o[k] = make_uint4(pk_bf16(y[8 * k], y[8 * k + 1]), pk_bf16(y[8 * k + 2], y[8 * k + 3]),
+                            pk_bf16(y[8 * k + 4], y[8 * k + 5]), pk_bf16(y[8 * k + 6], y[8 * k + 7]));
+      }
+      if (blk == 0) {
+#pragma unroll
+        for (int j = 0; j < T_J1; ++j)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) w[j][k] = from_upper_half(w[j][k]);
+      }
+    }
   }
 }
 
@@ -1747,25 +1757,18 @@ bool conv1_out(const uint16_t* Wb, const float* X, const float* bias, float* Y, 
   L1(k_conv1_out, N, Wb, X, bias, Y, C, N);
   return true;
 }
-bool tconv(const uint16_t* Wb, int Co, const void* X, bool x_bf16, int C, int Tin, int Tout, int KT, int S, int P,
-           long long Np, const float* bias, bool relu, void* Y, int y_bf16, hipStream_t st) {
-  const long long N = (long long)Tout * Np;
-  const int K = C * KT;
-  if (!x_bf16 || Co > 32 || Np % 8 || N > 0x7fffffffLL || ((uintptr_t)Wb & 15) || ((uintptr_t)X & 15) ||
-      ((uintptr_t)Y & 15) || (y_bf16 == 2 && (Co % 16 || Tout != 1)))
+bool temporal(const uint16_t* frames, int L, const TemporalLayer (&t)[3], uint16_t* a3h, float* x0, float* a1, float* a2,
+              float* a3, int Bn, long long HW, hipStream_t st) {
+  const long long Np = (long long)Bn * HW;
+  if (L != T_L || t[0].rows != T_C || t[0].cols != T_KT || t[1].rows != T_C || t[1].cols != T_K || t[2].rows != T_C ||
+      t[2].cols != T_K || Np % 64 || Np > (1 << 22) * (a3h ? 512LL : 1LL) || ((uintptr_t)t[1].w & 15) || ((uintptr_t)t[2].w & 15) || ((uintptr_t)a3h & 15))
     return false;
-  Im2col ic{};
-  ic.TX = X;
-  ic.Tin = Tin;
-  ic.KT = KT;
-  ic.S = S;
-  ic.P = P;
-  ic.out_h = y_bf16;
-  ic.Np = Np;
-  const long long tiles = (N + 127) / 128;
-  ic.xcd = Tout > 1 && Np % 128 == 0 && tiles % 8 == 0;   // tile order of the kernel's GV_TCONV remap
-  hipLaunchKernelGGL((k_gemm_v<32, GV_TCONV>), dim3((unsigned)tiles, 1), dim3(256), 0, st, Wb, (long long)K,
-                     nullptr, 0LL, ic, static_cast<float*>(Y), N, Co, (int)N, K, 0, bias, (int)relu);
+  Temporal q{frames, t[0].w, t[1].w, t[2].w, t[0].b, t[1].b, t[2].b, a3h, x0, a1, a2, a3, Bn, HW};
+  const dim3 grid((unsigned)std::min<long long>((Np / 64 + 3) / 4, kTemporalGrid));
+  if (a3h)
+    hipLaunchKernelGGL(k_temporal<false>, grid, dim3(256), 0, st, q);
+  else
+    hipLaunchKernelGGL(k_temporal<true>, grid, dim3(256), 0, st, q);
   return true;
 }
 
@@ -1810,14 +1813,6 @@ void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, bool acc
 }
 void tnorm(const uint16_t* frames, float* out, int Bn, int L, long long HW, hipStream_t st) {
   L1(k_tnorm, (long long)Bn * HW, frames, out, Bn, L, HW);
-}
-bool tconv1_h(const uint16_t* frames, int L, const uint16_t* Wb, int Co, int KT, const float* bias, uint16_t* a1,
-              int Bn, long long HW, hipStream_t st) {
-  const long long Np = (long long)Bn * HW;
-  if (L != T1_L || Co != 32 || KT != T1_K || Np % 64 || ((uintptr_t)a1 & 15)) return false;
-  const long long waves = Np / 64;
-  hipLaunchKernelGGL(k_tconv1_h, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, frames, Wb, bias, a1, Bn, HW);
-  return true;
 }
 void im2col1(const float* in, uint16_t* col, int C, int Tin, int Tout, int KT, int S, int P, long long N,
              hipStream_t st) {

@@ -357,6 +357,14 @@ hipError_t conv3_bwd(seg_nn* n, Grads& g, int id, const float* X, const float* d
   return e;
 }
 
+struct TemporalLayers {
+  TemporalLayer t[3];
+};
+TemporalLayers temporal_layers(seg_nn* n) {
+  auto l = [&](int id) { return TemporalLayer{wbf(n, id), bias(n, id), n->P[id].rows, n->P[id].cols}; };
+  return {{l(T1), l(T2), l(T3)}};
+}
+
 hipError_t forward(seg_nn* n, const uint16_t* frames, const float* stin, int Bn, hipStream_t st) {
   const Plan& p = n->plan;
   const int H = p.H, W = p.W;
@@ -373,19 +381,20 @@ hipError_t forward(seg_nn* n, const uint16_t* frames, const float* stin, int Bn,
     st_norm(stin, x0, Bn, HW, st);
     unet_in = x0;
   } else {
-    tnorm(frames, x0, Bn, L, HW, st);
-    // temporal convolutions
     float* a1 = at<float>(n, p.a1);
-    im2col1(x0, col, 1, L, 10, 5, 5, 0, N, st);
-    chk(gemm_wx(n, T1, col, true, 10 * N, a1, st));
-    bias_act(a1, bias(n, T1), 32, 10 * N, true, st);
     float* a2 = at<float>(n, p.a2);
-    im2col1(a1, col, 32, 10, 5, 5, 2, 2, N, st);
-    chk(gemm_wx(n, T2, col, true, 5 * N, a2, st));
-    bias_act(a2, bias(n, T2), 32, 5 * N, true, st);
     float* a3 = at<float>(n, p.a3);
-    chk(gemm_wx(n, T3, a2, false, N, a3, st));     // a2 viewed as [160][N]
-    bias_act(a3, bias(n, T3), 32, N, true, st);
+    if (!temporal(frames, L, temporal_layers(n).t, nullptr, x0, a1, a2, a3, Bn, HW, st)) {
+      tnorm(frames, x0, Bn, L, HW, st);
+      im2col1(x0, col, 1, L, 10, 5, 5, 0, N, st);
+      chk(gemm_wx(n, T1, col, true, 10 * N, a1, st));
+      bias_act(a1, bias(n, T1), 32, 10 * N, true, st);
+      im2col1(a1, col, 32, 10, 5, 5, 2, 2, N, st);
+      chk(gemm_wx(n, T2, col, true, 5 * N, a2, st));
+      bias_act(a2, bias(n, T2), 32, 5 * N, true, st);
+      chk(gemm_wx(n, T3, a2, false, N, a3, st));     // a2 viewed as [160][N]
+      bias_act(a3, bias(n, T3), 32, N, true, st);
+    }
     unet_in = a3;
   }
   // U-Net encoder
@@ -463,17 +472,8 @@ bool forward_infer(seg_nn* n, const uint16_t* frames, const float* stin, int Bn,
     st_norm(stin, x0, Bn, HW, st);
     unet_in = x0;
   } else {
-    // the frame normalisation runs inside the first temporal convolution;
-    // the other two gather their im2col as they load it, with bias and ReLU
-    // in the product's epilogue; a1, a2 and a3 are stored as BF16 (their
-    // consumers round them to BF16), a3 in channel blocks for the U-Net
-    uint16_t* a1 = at<uint16_t>(n, p.a1);
-    uint16_t* a2 = at<uint16_t>(n, p.a2);
-    uint16_t* a3 = at<uint16_t>(n, p.a3);
-    if (!(tconv1_h(frames, L, wbf(n, T1), n->P[T1].rows, n->P[T1].cols, bias(n, T1), a1, Bn, HW, st) &&
-          tconv(wbf(n, T2), 32, a1, true, 32, 10, 5, 5, 2, 2, N, bias(n, T2), true, a2, 1, st) &&
-          tconv(wbf(n, T3), 32, a2, true, 32, 5, 1, 5, 1, 0, N, bias(n, T3), true, a3, 2, st)))
-      return false;
+    uint16_t* a3 = at<uint16_t>(n, p.a3);   // BF16 in channel blocks, as the U-Net's convolutions take it
+    if (!temporal(frames, L, temporal_layers(n).t, a3, nullptr, nullptr, nullptr, nullptr, Bn, HW, st)) return false;
     unet_in = a3;
     unet_bf16 = true;
   }

@@ -68,15 +68,21 @@ struct ConvEpi {
 // does not fit the halo tiles.
 bool conv3_h(const uint16_t* Wb, const uint16_t* Wr, const void* X, bool x_bf16, uint16_t* Y, int Co, int Ci, int Bn,
              int H, int W, const float* bias, bool relu, int mode, const ConvEpi& ep, hipStream_t st);
-// A temporal convolution as one product without an im2col matrix:
-// Y [Co][Tout Np] = W [Co][C KT] (BF16) times the 1-D im2col of BF16
-// X [C][Tin][Np] that im2col1 would write (rounded), plus bias and ReLU,
-// stored as FP32 (y_bf16 = 0), as BF16 row-major (1) or, with one output
-// sample, as BF16 in channel blocks of 16 (2, Co a multiple of 16); the same
-// MFMA sums as im2col1 + gemm + bias_act. False (nothing launched) unless
-// x_bf16, Co <= 32, Np is a multiple of 8 and W, X, Y are 16-byte aligned.
-bool tconv(const uint16_t* Wb, int Co, const void* X, bool x_bf16, int C, int Tin, int Tout, int KT, int S, int P,
-           long long Np, const float* bias, bool relu, void* Y, int y_bf16, hipStream_t st);
+// The frame normalisation and the three temporal layers (weights [32][5],
+// [32][160], [32][160], each with bias and ReLU) in one pass over the frames
+// [Bn][50][HW]: with a3h the last activation as BF16 in channel blocks of 16,
+// else, for training, the normalised frames x0 [50][Bn HW] and the activations
+// a1 [32][10][Bn HW], a2 [32][5][Bn HW] and a3 [32][Bn HW] in FP32; the same
+// values as tnorm, im2col1, gemm and bias_act. False (nothing launched) unless
+// the layers have these shapes, L = 50, Bn HW is a multiple of 64, the second
+// and third weights and a3h are 16-byte aligned.
+struct TemporalLayer {
+  const uint16_t* w;
+  const float* b;
+  int rows, cols;
+};
+bool temporal(const uint16_t* frames, int L, const TemporalLayer (&t)[3], uint16_t* a3h, float* x0, float* a1, float* a2,
+              float* a3, int Bn, long long HW, hipStream_t st);
 // The first two 3 x 3 convolutions of the summary U-Net in one pass: e1a
 // (W1 [32][2 9], bias b1, ReLU) on the planar FP32 input X [2][Bn][H][W],
 // kept in LDS, then e1b (W2r: its conv3_reorder copy, bias b2, ReLU) with
@@ -95,13 +101,6 @@ void conv3_reorder(const uint16_t* Wb, uint16_t* Wr, int Co, int Ci, hipStream_t
 size_t conv3_reordered_size(int Co, int Ci);
 void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, bool acc, hipStream_t st);
 void tnorm(const uint16_t* frames, float* out, int Bn, int L, long long HW, hipStream_t st);
-// tnorm and the first temporal convolution (W [32][5], stride 5, no padding,
-// bias and ReLU) in one pass for inference, a1 [32][10][Bn HW] as BF16: the
-// same values as tnorm, im2col1, gemm and bias_act rounded to BF16. False
-// (nothing launched) unless L = 50, Co = 32, KT = 5, Bn HW is a multiple of
-// 64 and a1 is 16-byte aligned.
-bool tconv1_h(const uint16_t* frames, int L, const uint16_t* Wb, int Co, int KT, const float* bias, uint16_t* a1,
-              int Bn, long long HW, hipStream_t st);
 void im2col1(const float* in, uint16_t* col, int C, int Tin, int Tout, int KT, int S, int P, long long N,
              hipStream_t st);
 void col2im1(const float* dcol, float* din, int C, int Tin, int Tout, int KT, int S, int P, long long N,
