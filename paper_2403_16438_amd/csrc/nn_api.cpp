@@ -612,15 +612,21 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* ga2 = at<float>(n, p.ga2);
   bias_mask(ga3, a3, g.bias(n, T3), 32, N, st);
   chk(lin_dw(n, g, T3, ga3, a2, N, st));
-  chk(gemm_wtdy(n, T3, ga3, N, ga2, st));
   float* a1 = at<float>(n, p.a1);
   float* ga1 = at<float>(n, p.ga1);
-  float* dcol = at<float>(n, p.dcol);
-  bias_mask(ga2, a2, g.bias(n, T2), 32, 5 * N, st);
-  chk(temporal_dw(n, g, T2, ga2, a1, 32, 10, 5, 2, 2, N, st));
-  chk(gemm_wtdy(n, T2, ga2, 5 * N, dcol, st));
-  col2im1(dcol, ga1, 32, 10, 5, 5, 2, 2, N, st);
-  bias_mask(ga1, a1, g.bias(n, T1), 32, 10 * N, st);
+  if (temporal_dx(wbf(n, T2), wbf(n, T3), ga3, a2, a1, ga2, ga1, N, st)) {   // masked
+    bias_mask(ga2, nullptr, g.bias(n, T2), 32, 5 * N, st);
+    chk(temporal_dw(n, g, T2, ga2, a1, 32, 10, 5, 2, 2, N, st));
+    bias_mask(ga1, nullptr, g.bias(n, T1), 32, 10 * N, st);
+  } else {
+    chk(gemm_wtdy(n, T3, ga3, N, ga2, st));
+    float* dcol = at<float>(n, p.dcol);
+    bias_mask(ga2, a2, g.bias(n, T2), 32, 5 * N, st);
+    chk(temporal_dw(n, g, T2, ga2, a1, 32, 10, 5, 2, 2, N, st));
+    chk(gemm_wtdy(n, T2, ga2, 5 * N, dcol, st));
+    col2im1(dcol, ga1, 32, 10, 5, 5, 2, 2, N, st);
+    bias_mask(ga1, a1, g.bias(n, T1), 32, 10 * N, st);
+  }
   chk(temporal_dw(n, g, T1, ga1, at<float>(n, p.x0), 1, L, 10, 5, 0, N, st));
   grad_reduce(g.t, at<float>(n, p.grad), st);
   chk(hipGetLastError());

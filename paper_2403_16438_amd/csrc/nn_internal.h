@@ -116,6 +116,12 @@ void rmsprop(float* w, const float* g, float* v, uint16_t* wb, long long n, floa
 void to_bf16_copy(const float* w, uint16_t* wb, long long n, hipStream_t st);
 
 // ---- backward pass (k_nn_bwd.hip) ----
+// The temporal layers' input gradients: g2 [32][5][N] and g1 [32][10][N] from
+// the third layer's masked output gradient g3 [32][N] and the weights [32][160]
+// of the second and third layer, masked by the activations a2 and a1. False
+// (nothing launched) unless N is a multiple of 32 (and at most 2^22).
+bool temporal_dx(const uint16_t* w2, const uint16_t* w3, const float* g3, const float* a2, const float* a1, float* g2,
+                 float* g1, long long N, hipStream_t st);
 // Weight gradients are sums over pixels K, formed in at most kGradSplits
 // ranges of grad_chunk(K) pixels whose partial sums grad_reduce adds in order.
 constexpr int kGradSplits = 32;

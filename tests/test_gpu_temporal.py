@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2403_16438_amd.surrogate import Surrogate, he_init
+from paper_2403_16438_amd.surrogate import Surrogate, he_init, param_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +36,29 @@ def test_batched_equals_single(B, H, W):
         torch.cuda.synchronize()
         assert torch.equal(got[b], ref), (b, (got[b] - ref).abs().max().item())
     one.close()
+
+
+@pytest.mark.parametrize("H,W", [(4, 4), (12, 12), (20, 36)])
+def test_gradients_of_copies(H, W):
+    """One segment, whose pixel count is no multiple of 32, takes the products,
+    the gather and the mask passes of the temporal input gradients; 16 copies
+    take the one kernel. The loss is a mean, so the gradients agree up to the
+    FP32 order of the sums over pixels (at most 2,048 terms in groups of 16,
+    each rounding by 2^-24 of a partial sum): below 1e-4 norm-wise."""
+    assert (H * W) % 32
+    rng = np.random.default_rng(H * 40 + W)
+    frames = rng.poisson(1000, size=(1, 50, H, W)).astype(np.uint16)
+    frames[:, 20:23, 1:3, 1:3] += 250
+    labels = np.zeros((1, H, W), np.float32)
+    labels[:, 1:3, 1:3] = 1
+    theta = he_init(9)
+    got = []
+    for B in (1, 16):
+        net = Surrogate(B, H, W, theta)
+        _, g = net.backward(torch.from_numpy(np.repeat(frames, B, 0).view(np.int16)).cuda(),
+                            torch.from_numpy(np.repeat(labels, B, 0)).cuda(), want_grad=True)
+        got.append(g.cpu().numpy().astype(np.float64))
+        net.close()
+    for name, r, c, wo, bo in param_layout():
+        sl = slice(wo, bo + (r // 4 if name in ("u2", "u1") else r))
+        assert np.linalg.norm(got[1][sl] - got[0][sl]) <= 1e-4 * np.linalg.norm(got[0][sl]), name
