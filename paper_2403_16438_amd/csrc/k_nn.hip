@@ -296,18 +296,29 @@ __global__ __launch_bounds__(256) void k_gemm_v(const uint16_t* __restrict__ A, 
 // and the nine offsets read it from LDS.
 constexpr int HC = 16;                          // input channels per chunk
 constexpr int HX = 6336;                        // largest halo tile: 6 x 66 x 16
-// Convolution weights reordered for k_conv3_halo: Wr[chunk][co][ky 3 + kx][cl]
-// = W[co][9 (16 chunk + cl) + ky 3 + kx] (0 past Ci), so that a chunk's
-// weights of one output channel are 144 contiguous values.
-__global__ void k_conv3_reorder(const uint16_t* __restrict__ Wb, uint16_t* __restrict__ Wr, int Co, int Ci) {
-  const int nch = (Ci + HC - 1) / HC;
-  const long long total = (long long)nch * Co * 9 * HC;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int cl = (int)(i % HC), kyx = (int)((i / HC) % 9), co = (int)((i / (9 * HC)) % Co),
-            ch = (int)(i / ((long long)9 * HC * Co));
-  const int c = ch * HC + cl;
-  Wr[i] = c < Ci ? Wb[(long long)co * Ci * 9 + c * 9 + kyx] : (uint16_t)0;
+// Copies of every 3 x 3 layer's weights in one launch (a launch per layer and
+// copy, twenty in a training step, took 50 us and the gaps between them):
+// Wr[chunk][co][ky 3 + kx][cl] = W[co][9 (16 chunk + cl) + ky 3 + kx] (0 past
+// Ci) for k_conv3_halo, so that a chunk's weights of one output channel are
+// 144 contiguous values, and, where Ci is a multiple of 32, Wd [Ci / 32][9]
+// [Co / 16][lane][8] for k_dx3: output channel 16 block + 8 (lane / 32) + q and
+// input channel 32 block + lane % 32 of each tap, a wave's operand in a row.
+__global__ __launch_bounds__(256) void k_conv3_reorder(ReorderTable t) {
+  int k = 0;
+  while (k + 1 < t.n && t.l[k + 1].block0 <= (int)blockIdx.x) ++k;
+  const ReorderLayer& l = t.l[k];
+  const int Co = l.Co, Ci = l.Ci, i = ((int)blockIdx.x - l.block0) * 256 + threadIdx.x;
+  if (i >= (Ci + HC - 1) / HC * HC * Co * 9) return;
+  {
+    const int cl = i % HC, kyx = i / HC % 9, co = i / (9 * HC) % Co, c = i / (9 * HC * Co) * HC + cl;
+    l.Wr[i] = c < Ci ? l.Wb[(long long)co * Ci * 9 + c * 9 + kyx] : (uint16_t)0;
+  }
+  if (l.Wd) {
+    const int q = i & 7, lane = i >> 3 & 63, rest = i >> 9, CG = Co / 16;
+    const int cg = rest % CG, tap = rest / CG % 9, blk = rest / CG / 9;
+    const int co = 16 * cg + 8 * (lane >> 5) + q, c = 32 * blk + (lane & 31);
+    l.Wd[i] = l.Wb[(long long)co * Ci * 9 + c * 9 + tap];
+  }
 }
 
 // Tile of this workgroup: the dispatcher deals workgroups to the eight XCDs
@@ -1648,8 +1659,13 @@ hipError_t gemm(const GemmOp& g, hipStream_t st) {
 
 #define L1(kernel, n, ...) hipLaunchKernelGGL(kernel, grid1(n), dim3(256), 0, st, __VA_ARGS__)
 
-void conv3_reorder(const uint16_t* Wb, uint16_t* Wr, int Co, int Ci, hipStream_t st) {
-  L1(k_conv3_reorder, (long long)((Ci + HC - 1) / HC) * Co * 9 * HC, Wb, Wr, Co, Ci);
+void conv3_reorder(ReorderTable& t, hipStream_t st) {
+  int blocks = 0;
+  for (int k = 0; k < t.n; ++k) {
+    t.l[k].block0 = blocks;
+    blocks += (int)((conv3_reordered_size(t.l[k].Co, t.l[k].Ci) + 255) / 256);
+  }
+  if (blocks) hipLaunchKernelGGL(k_conv3_reorder, dim3(blocks), dim3(256), 0, st, t);
 }
 size_t conv3_reordered_size(int Co, int Ci) { return (size_t)((Ci + HC - 1) / HC) * Co * 9 * HC; }
 

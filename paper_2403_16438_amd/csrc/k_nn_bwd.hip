@@ -560,17 +560,6 @@ __global__ __launch_bounds__(256) void k_dx3(const uint16_t* __restrict__ Wd, co
   }
 }
 
-// Wd [Ci / 32][9][Co / 16][lane][8] from W [Co][Ci 9]: lane l holds output
-// channels 16 cg + 8 (l >> 5) + 0..7 of input channel 32 block + (l & 31)
-__global__ void k_reorder_dx(const uint16_t* __restrict__ Wb, uint16_t* __restrict__ Wd, int Co, int Ci) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Co * Ci * 9) return;
-  const int q = i & 7, lane = i >> 3 & 63, rest = i >> 9, CG = Co / 16;
-  const int cg = rest % CG, tap = rest / CG % 9, blk = rest / CG / 9;
-  const int co = 16 * cg + 8 * (lane >> 5) + q, c = 32 * blk + (lane & 31);
-  Wd[i] = Wb[(long long)co * Ci * 9 + c * 9 + tap];
-}
-
 template <int CG, int NTW>
 hipError_t launch_dx3(const uint16_t* Wd, const float* dY, float* dX, int Ci, int Bn, int H, int W, hipStream_t st) {
   const int BC = std::min(W, 64), BR = 128 * NTW / BC, np = (BR + 2) * (BC + 2);
@@ -647,10 +636,6 @@ bool temporal_dx(const uint16_t* w2, const uint16_t* w3, const float* g3, const 
 void grad_reduce(const GradTable& t, float* grad, hipStream_t st) {
   const int ch = t.nb ? t.b[t.nb - 1].ch0 + t.b[t.nb - 1].C : 0;
   hipLaunchKernelGGL(k_grad_reduce, dim3(t.wblocks + (ch + 3) / 4), dim3(256), 0, st, t, grad);
-}
-
-void reorder_dx(const uint16_t* Wb, uint16_t* Wd, int Co, int Ci, hipStream_t st) {
-  hipLaunchKernelGGL(k_reorder_dx, dim3((Co * Ci * 9 + 255) / 256), dim3(256), 0, st, Wb, Wd, Co, Ci);
 }
 
 bool dx3(const uint16_t* Wd, const float* dY, float* dX, int Co, int Ci, int Bn, int H, int W, hipStream_t st,

@@ -83,7 +83,7 @@ struct Plan {
   Buf wb, grad, vel;   // BF16 weights, FP32 gradients, RMSProp state
   Buf wr;              // 3 x 3 convolution weights reordered for the direct kernel
   size_t wr_off[NPAR]; // element offset of each 3 x 3 layer in wr
-  Buf wd;              // and for its input gradient (reorder_dx), the same offsets
+  Buf wd;              // and for its input gradient, the same offsets
   Buf part, bpart;     // partial sums of the weight and bias gradients
   size_t total;
 };
@@ -208,12 +208,14 @@ const float* bias(seg_nn* n, int id) { return n->params + n->po.b[id]; }
 
 // refreshes the reordered copy of every 3 x 3 convolution's BF16 weights
 void reorder_conv3(seg_nn* n, hipStream_t st) {
+  ReorderTable t{};
   for (int id = E1A; id < NPAR; ++id)
     if (id != U2 && id != U1 && id != FO) {
       const int Co = n->P[id].rows, Ci = n->P[id].cols / 9;
-      conv3_reorder(wbf(n, id), at<uint16_t>(n, n->plan.wr) + n->plan.wr_off[id], Co, Ci, st);
-      if (Ci % 32 == 0) reorder_dx(wbf(n, id), at<uint16_t>(n, n->plan.wd) + n->plan.wr_off[id], Co, Ci, st);
+      t.l[t.n++] = ReorderLayer{wbf(n, id), at<uint16_t>(n, n->plan.wr) + n->plan.wr_off[id],
+                                Ci % 32 == 0 ? at<uint16_t>(n, n->plan.wd) + n->plan.wr_off[id] : nullptr, Co, Ci, 0};
     }
+  conv3_reorder(t, st);
 }
 float* gw(seg_nn* n, int id) { return at<float>(n, n->plan.grad) + n->po.w[id]; }
 

@@ -96,8 +96,20 @@ bool conv3_first2_h(const uint16_t* W1, const float* b1, int Co1, int Ci1, const
 // (nothing launched) unless Co is 32 or 64 and Ci 64 or 128.
 bool up2_h(const uint16_t* Wb, const uint16_t* X, const float* bias, uint16_t* Y, int Co, int Ci, int Bn, int h, int w,
            hipStream_t st);
-// Wr [ceil(Ci / 16)][Co][9][16] from W [Co][Ci 9] (zero past Ci)
-void conv3_reorder(const uint16_t* Wb, uint16_t* Wr, int Co, int Ci, hipStream_t st);
+// Copies of 3 x 3 weights W [Co][Ci 9], all layers in one launch: Wr
+// [ceil(Ci / 16)][Co][9][16] (zero past Ci) and, unless null (Ci a multiple of
+// 32, Co of 16), Wd [Ci / 32][9][Co / 16][64][8] for dx3, of the same size.
+struct ReorderLayer {
+  const uint16_t* Wb;
+  uint16_t *Wr, *Wd;
+  int Co, Ci;
+  int block0;   // set by conv3_reorder
+};
+struct ReorderTable {
+  int n;
+  ReorderLayer l[10];
+};
+void conv3_reorder(ReorderTable& t, hipStream_t st);
 size_t conv3_reordered_size(int Co, int Ci);
 void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, bool acc, hipStream_t st);
 void tnorm(const uint16_t* frames, float* out, int Bn, int L, long long HW, hipStream_t st);
@@ -164,12 +176,11 @@ bool dw3(const float* dY, const float* X, float* P, int Co, int Ci, int Bn, int 
 // are 16-byte aligned.
 bool dw1(const float* dY, const float* X, float* P, int M, int R, long long K, int Tin, int KT, int S, int Pd,
          long long Np, hipStream_t st);
-// Input gradient of a 3 x 3 convolution, with Wd from reorder_dx (Ci a
+// Input gradient of a 3 x 3 convolution, with Wd from conv3_reorder (Ci a
 // multiple of 32); false (nothing launched) unless Co is 32, 64 or 128, Ci a
 // multiple of 32 and W 8, 16, 32, 64 or a larger multiple of 8.
 bool dx3(const uint16_t* Wd, const float* dY, float* dX, int Co, int Ci, int Bn, int H, int W, hipStream_t st,
          hipError_t* err);
-void reorder_dx(const uint16_t* Wb, uint16_t* Wd, int Co, int Ci, hipStream_t st);
 
 // summary-image input (S, T): st [Bn][2][HW] -> x [2][Bn HW] with channel 0
 // the patch-standardised S and channel 1 T / sqrt(S + 25)
