@@ -104,14 +104,15 @@ __global__ __launch_bounds__(256) void k_bias_mask(float* __restrict__ dY, const
 // operand is one aligned 16-byte LDS read: X is loaded three times (once per
 // ky) instead of being written and read as nine rows. The chain over a
 // range's pixels is serial by the order of its sum, so what counts is the
-// time per step: long steps (256 pixels for 32 output channels, 128 for 64)
-// with the next step's loads in flight, and twice as many waves loading as
-// computing where RT = 1. The ten 3 x 3 layers of a step of 32 patches of
-// 64 x 64 take 223 us; the product on an im2col matrix took 2,358 us and
-// writing that matrix 476 us. (The matrix cores need 19 us for these layers.)
-constexpr int DW_T = 384;   // 6 waves
-
-template <int RT, int KS>
+// time per step: long steps with the next step's loads in flight, and more
+// waves loading than computing. Where fewer workgroups than compute units are
+// launched (three quarters, to leave some margin) a step is 512 pixels for 32
+// output channels and 256 for 64, with twelve waves; else half of each, with
+// six, so that two workgroups share a compute unit. The ten 3 x 3 layers of a
+// step of 32 patches of 64 x 64 take 209 us (221 with the short steps alone);
+// the product on an im2col matrix took 2,358 us and writing that matrix 476 us.
+// (The matrix cores need 19 us for these layers.)
+template <int RT, int KS, int DW_T>
 __global__ __launch_bounds__(DW_T) void k_dw3(const float* __restrict__ dY, const float* __restrict__ X,
                                               float* __restrict__ P, int Co, int Ci, int H, int W, int K,
                                               int kchunk) {
@@ -236,21 +237,24 @@ __global__ __launch_bounds__(DW_T) void k_dw3(const float* __restrict__ dY, cons
 // r = c KT + tap, column q = j Np + n: X[c][j S + tap - Pd][n], zero outside
 // 0 .. Tin - 1) that im2col1 writes, or X itself (KT = 1, S = 0, Tin = 1,
 // Np = K). A workgroup takes one range of columns, 32 RT rows of dY and 32
-// rows r; wave w computes row tile w, all four waves load.
-template <int RT, int KS>
-__global__ __launch_bounds__(256) void k_dw1(const float* __restrict__ dY, const float* __restrict__ X,
+// rows r; wave w computes row tile w, all waves load. 32 rows of dY take steps
+// of 512 columns with eight waves: the temporal layers' and the output layer's
+// gradients of 16 segments of 64 x 64, 190 us with 256 and four, take 147
+// (1,024 and sixteen are no faster).
+template <int RT, int KS, int NT>
+__global__ __launch_bounds__(NT) void k_dw1(const float* __restrict__ dY, const float* __restrict__ X,
                                              float* __restrict__ P, int M, int R, int K, int kchunk, int Tin, int KT,
                                              int S, int Pd, int Np) {
   constexpr int G = KS / 8;
-  constexpr int AI = RT * 32 * G / 256, BI = 32 * G / 256;
+  constexpr int AI = RT * 32 * G / NT, BI = 32 * G / NT;
   static_assert(BI >= 1, "32 rows fill the workgroup");
   __shared__ __attribute__((aligned(16))) uint16_t As[RT * 32][KS + 8];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[32][KS + 8];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int r0 = blockIdx.y * 32, m0 = blockIdx.z * 32 * RT;
   const int kbeg = blockIdx.x * kchunk, kend = min(K, kbeg + kchunk);
-  const int g = tid % G * 8, row0 = tid / G;         // rows row0 + j (256 / G)
-  constexpr int RS = 256 / G;
+  const int g = tid % G * 8, row0 = tid / G;         // rows row0 + j (NT / G)
+  constexpr int RS = NT / G;
   int q = kbeg + g, jj = q / Np, n = q - jj * Np;
   float4 av[AI][2], bv[BI][2];
   uint32_t bok = 0;
@@ -603,12 +607,18 @@ bool dw3(const float* dY, const float* X, float* P, int Co, int Ci, int Bn, int 
   if (W % 8 || Co % 32 || K > 0x3fffffffLL || ((uintptr_t)dY & 15) || ((uintptr_t)X & 15)) return false;
   const int kc = grad_chunk(K);
   const dim3 grid(grad_ranges(K), 3 * ((Ci + 31) / 32), Co <= 32 ? 1 : Co / 64);
-  if (Co <= 32)
-    hipLaunchKernelGGL((k_dw3<1, 256>), grid, dim3(DW_T), 0, st, dY, X, P, Co, Ci, H, W, (int)K, kc);
-  else if (Co % 64 == 0)
-    hipLaunchKernelGGL((k_dw3<2, 128>), grid, dim3(DW_T), 0, st, dY, X, P, Co, Ci, H, W, (int)K, kc);
+  if (Co > 32 && Co % 64) return false;
+  const bool big = grid.x * grid.y * grid.z <= 200;
+#define DW3(RT, KS, NT) hipLaunchKernelGGL((k_dw3<RT, KS, NT>), grid, dim3(NT), 0, st, dY, X, P, Co, Ci, H, W, (int)K, kc)
+  if (Co <= 32 && big)
+    DW3(1, 512, 768);
+  else if (Co <= 32)
+    DW3(1, 256, 384);
+  else if (big)
+    DW3(2, 256, 768);
   else
-    return false;
+    DW3(2, 128, 384);
+#undef DW3
   return true;
 }
 
@@ -616,12 +626,14 @@ bool dw1(const float* dY, const float* X, float* P, int M, int R, long long K, i
          long long Np, hipStream_t st) {
   if (Np % 8 || K % 8 || K > 0x3fffffffLL || ((uintptr_t)dY & 15) || ((uintptr_t)X & 15)) return false;
   const int kc = grad_chunk(K), z = grad_ranges(K), rb = (R + 31) / 32;
+#define DW1(RT, KS, NT)                                                                                           \
+  hipLaunchKernelGGL((k_dw1<RT, KS, NT>), dim3(z, rb, (M + 32 * RT - 1) / (32 * RT)), dim3(NT), 0, st, dY, X, P, M, R, \
+                     (int)K, kc, Tin, KT, S, Pd, (int)Np)
   if (M <= 32)
-    hipLaunchKernelGGL((k_dw1<1, 256>), dim3(z, rb, 1), dim3(256), 0, st, dY, X, P, M, R, (int)K, kc, Tin, KT, S, Pd,
-                       (int)Np);
+    DW1(1, 512, 512);
   else
-    hipLaunchKernelGGL((k_dw1<2, 128>), dim3(z, rb, (M + 63) / 64), dim3(256), 0, st, dY, X, P, M, R, (int)K, kc, Tin,
-                       KT, S, Pd, (int)Np);
+    DW1(2, 128, 256);
+#undef DW1
   return true;
 }
 
