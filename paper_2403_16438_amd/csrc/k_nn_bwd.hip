@@ -368,6 +368,44 @@ __global__ __launch_bounds__(256) void k_grad_reduce(GradTable t, float* __restr
   if (lane == 0) grad[b.out + c] = v;
 }
 
+// ------------------------------------- input gradient, transposed convolutions
+// dX [M][N] = W^T dY for W [K][M] (BF16) and dY [K][N], the depth in steps of
+// 16 as the tiled product takes it. A wave takes 32 rows x 32 columns and reads
+// both operands from memory itself: the row tiles of one column block are
+// neighbouring waves, so a second read of dY comes from the caches, and with no
+// barrier every load of four depth steps is in flight at once. Latency is what
+// bounds it (a few thousand columns, 8 or 16 steps): the two layers of a step of
+// 32 patches of 64 x 64 take 17 us; the tiled product, which waits for its
+// loads at each of its steps, took 58.
+__global__ __launch_bounds__(256) void k_lin_dx(const uint16_t* __restrict__ W, const float* __restrict__ dY,
+                                                float* __restrict__ dX, int M, int K, int N) {
+  const int lane = threadIdx.x & 63, h = lane >> 5, l = lane & 31;
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6), tiles = M / 32;
+  const int m0 = w % tiles * 32, n = w / tiles * 32 + l;
+  if (n - l >= N) return;
+  const float* y = dY + (long long)8 * h * N + min(n, N - 1);
+  const uint16_t* a = W + 8 * h * M + m0 + l;
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll 4
+  for (int g = 0; g < K / 16; ++g) {
+    uint32_t aw[4], bw[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = 16 * g + 2 * q;
+      aw[q] = a[k * M] | (uint32_t)a[(k + 1) * M] << 16;
+      bw[q] = pk(y[(long long)k * N], y[(long long)(k + 1) * N]);
+    }
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(aw[0], aw[1], aw[2], aw[3])),
+                                                  __builtin_bit_cast(bf16x8, make_uint4(bw[0], bw[1], bw[2], bw[3])),
+                                                  acc, 0, 0, 0);
+  }
+  if (n >= N) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) dX[(long long)(m0 + 8 * (i >> 2) + 4 * h + (i & 3)) * N + n] = acc[i];
+}
+
 // ------------------------------------------- input gradients, temporal layers
 // From the third layer's output gradient g3 [32][N] (masked) to the second's,
 // g2 [32][5][N] = W3^T g3, and to the first's, g1 [32][10][N], both masked
@@ -635,6 +673,11 @@ bool dw1(const float* dY, const float* X, float* P, int M, int R, long long K, i
     DW1(2, 128, 256);
 #undef DW1
   return true;
+}
+
+void lin_dx(const uint16_t* W, const float* dY, float* dX, int M, int K, long long N, hipStream_t st) {
+  const long long waves = (N + 31) / 32 * (M / 32);
+  hipLaunchKernelGGL(k_lin_dx, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, W, dY, dX, M, K, (int)N);
 }
 
 bool temporal_dx(const uint16_t* w2, const uint16_t* w3, const float* g3, const float* a2, const float* a1, float* g2,

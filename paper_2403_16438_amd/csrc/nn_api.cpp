@@ -554,7 +554,7 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   bias_mask(gcat1, nullptr, g.bias(n, U1), 32, N, st);
   up_gather(gcat1, gz1, 32, Bn, H / 2, W / 2, st);
   chk(lin_dw(n, g, U1, gz1, d2, N2, st));
-  chk(gemm_wtdy(n, U1, gz1, N2, gd2, st));
+  lin_dx(wbf(n, U1), gz1, gd2, n->P[U1].cols, n->P[U1].rows, N2, st);
   // d2b, d2a
   float* d2a = at<float>(n, p.d2a);
   float* gd2a = at<float>(n, p.gd2a);
@@ -571,7 +571,7 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   bias_mask(gcat2, nullptr, g.bias(n, U2), 64, N2, st);
   up_gather(gcat2, gz2, 64, Bn, H / 4, W / 4, st);
   chk(lin_dw(n, g, U2, gz2, b3, N4, st));
-  chk(gemm_wtdy(n, U2, gz2, N4, gb3, st));
+  lin_dx(wbf(n, U2), gz2, gb3, n->P[U2].cols, n->P[U2].rows, N4, st);
   // bottleneck
   float* e3a = at<float>(n, p.e3a);
   float* ge3a = at<float>(n, p.ge3a);
