@@ -35,7 +35,8 @@
 // overwrite a slot after every workgroup of its component has read it (it
 // needs their next slots first), and the slots are cleared before each
 // launch, so a stale word never carries the expected tag. The launch is
-// cooperative, so all workgroups are resident; a wait is still bounded by a
+// cooperative (unless every component is one workgroup's: nothing is exchanged
+// then), so all workgroups are resident; a wait is still bounded by a
 // wall-clock limit, after which the component is marked abandoned, every
 // workgroup of it leaves, and the error flag is set.
 #include <algorithm>
@@ -47,9 +48,6 @@
 namespace seg {
 namespace {
 
-constexpr int CT = 1024;
-constexpr int CW = CT / 64;   // 16 waves
-constexpr int CV = CT - 64;   // waves 0..14 of the HALS product phases (wave 15: Gram)
 constexpr int R8 = kMaxRank;
 
 __device__ __forceinline__ double wsum(double v) {
@@ -133,6 +131,7 @@ __device__ __forceinline__ double chunk_sum(const double* x, size_t step, int n)
   return v;
 }
 
+template <int CW>
 __device__ double block_max(double v, double* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
@@ -145,6 +144,7 @@ __device__ double block_max(double v, double* red) {
 }
 
 // argmax with lowest index on ties
+template <int CW>
 __device__ void block_argmax(double v, int idx, double* red, int* redi, double* best, int* bidx) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int off = 32; off > 0; off >>= 1) {
@@ -174,6 +174,193 @@ __device__ void block_argmax(double v, int idx, double* red, int* redi, double* 
 
 using u64 = unsigned long long;
 
+// ---- short components: HALS with the rows of P_c in registers
+//
+// A component that one workgroup holds whole, of at most 512 pixels, 44
+// segments and rank 3: a thread of the first four waves keeps its one or two
+// rows of P_c and of F in registers, a lane its column of A, and a sweep has one
+// barrier. F^T P and F^T F are summed over a wave's rows by halving exchanges,
+// sixteen sums at a time (eight values against eight with the other half of the
+// wave, then four, two, one), over the waves through LDS; every wave then forms
+// the same A and takes its columns as scalars for the rows of P A^T. What
+// bounds it is the instructions of one wave per SIMD, the divisions' chains
+// among them. The NMF of a 64 x 64 x 1,000 recording (three components of 200
+// to 300 pixels, rank 1, 200 sweeps) takes 0.20 ms; with P_c in LDS, five
+// barriers a sweep and an exchange of slots between two workgroups it took
+// 0.90. At rank 2 and 370 pixels 0.75 against 1.14 ms (all eight waves with one
+// row each: 1.00; 1,024 threads and so half the registers: 1.07).
+constexpr int kRowsMax = 512, kRowsK = 44;   // and rank at most 3
+
+__device__ __forceinline__ double swap_add32(double a, double b) {
+  const u64 x = (u64)__double_as_longlong(a), y = (u64)__double_as_longlong(b);
+  const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double((long long)((u64)h[0] << 32 | l[0])) + __longlong_as_double((long long)((u64)h[1] << 32 | l[1]));
+}
+
+__device__ __forceinline__ double swap_add16(double a, double b) {
+  const u64 x = (u64)__double_as_longlong(a), y = (u64)__double_as_longlong(b);
+  const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  return __longlong_as_double((long long)((u64)h[0] << 32 | l[0])) + __longlong_as_double((long long)((u64)h[1] << 32 | l[1]));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double from_lane(double v) {
+  const u64 x = (u64)__double_as_longlong(v);
+  const int l = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, 0xf, 0xf, false);
+  const int h = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double((long long)((u64)(unsigned)h << 32 | (unsigned)l));
+}
+
+// sum of v[i] over the wave's lanes, in lanes 4 i .. 4 i + 3
+__device__ __forceinline__ double wave_sums(double (&v)[16], int lane) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = swap_add32(v[i], v[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = swap_add16(v[i], v[i + 4]);
+  const bool b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) v[i] = (b3 ? v[i + 2] : v[i]) + from_lane<0x128>(b3 ? v[i] : v[i + 2]);   // row_ror 8
+  double x = (b2 ? v[1] : v[0]) + from_lane<0x141>(b2 ? v[0] : v[1]);   // row_half_mirror: the other quad
+  x += from_lane<0x4e>(x);   // quad_perm 2, 3, 0, 1
+  x += from_lane<0xb1>(x);   // quad_perm 1, 0, 3, 2
+  return x;
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const u64 x = (u64)__double_as_longlong(v);
+  const unsigned l = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, lane);
+  const unsigned h = (unsigned)__builtin_amdgcn_readlane((int)(x >> 32), lane);
+  return __longlong_as_double((long long)((u64)h << 32 | l));
+}
+
+// doubles of LDS: two sets of the waves' sums
+__device__ __forceinline__ int rows_scratch(int ml, int K, int N) {
+  return 2 * min(4, (ml + 63) / 64) * N * ((K + N + 15) / 16 * 16);
+}
+
+// RP rows per thread of the first four waves, NR rank, KC blocks of 16
+// columns: K columns of P_c, and in the last NR the entries (n, n2) of F^T F,
+// n2 >= n
+template <int RP, int NR, int KC>
+__device__ void hals_rows(const float* Pl, int Kp, double* F, double* A, double* part, int ml, int K, int sweeps) {
+  constexpr int KW = 16 * KC, G0 = KW - NR;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, nwv = min(4, (ml + 63) >> 6);
+  const bool col = lane < K;
+  float p[RP][KW];
+  double f[RP][NR], av[NR];
+  bool row[RP];
+#pragma unroll
+  for (int u = 0; u < RP; ++u) {
+    const int m = t + 256 * u;
+    row[u] = t < 256 && m < ml;
+#pragma unroll
+    for (int i = 0; i < KW; ++i) p[u][i] = row[u] && i < K ? Pl[m * Kp + i] : 0.f;
+#pragma unroll
+    for (int n = 0; n < NR; ++n) f[u][n] = row[u] ? F[m * R8 + n] : 0.0;
+  }
+#pragma unroll
+  for (int n = 0; n < NR; ++n) av[n] = 0.0;
+  for (int sweep = -1; sweep < sweeps; ++sweep) {
+    double* set = part + (sweep & 1) * nwv * NR * KW;
+    if (wv < nwv) {
+#pragma unroll
+      for (int n = 0; n < NR; ++n)
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+          double v[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int k = 16 * c + i, n2 = k - G0;
+            if (n2 >= 0 && n2 < n) {   // (n2, n) is row n2's
+              v[i] = 0.0;
+              continue;
+            }
+#pragma unroll
+            for (int u = 0; u < RP; ++u) {
+              const double y = n2 >= 0 ? f[u][n2 < 0 ? 0 : n2] : (double)p[u][k];
+              v[i] = u == 0 ? f[u][n] * y : fma(f[u][n], y, v[i]);
+            }
+          }
+          const double x = wave_sums(v, lane);
+          if ((lane & 3) == 0) set[(wv * NR + n) * KW + 16 * c + (lane >> 2)] = x;
+        }
+    }
+    __syncthreads();
+    if (wv >= nwv) continue;
+    double tot[NR], g[NR][NR];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) {
+      const double* x = set + n * KW + min(lane, KW - 1);
+      tot[n] = x[0];
+      for (int w = 1; w < nwv; ++w) tot[n] += x[w * NR * KW];
+    }
+#pragma unroll
+    for (int n = 0; n < NR; ++n)
+#pragma unroll
+      for (int n2 = n; n2 < NR; ++n2) g[n][n2] = g[n2][n] = lane_value(tot[n], G0 + n2);
+#pragma unroll
+    for (int n = 0; n < NR; ++n)
+      if (g[n][n] > 0.0) {
+        double sg = 0.0;
+#pragma unroll
+        for (int n2 = 0; n2 < NR; ++n2) sg += g[n][n2] * av[n2];
+        av[n] = col ? fmax(0.0, av[n] + (tot[n] - sg) / g[n][n]) : 0.0;
+      }
+    if (sweep < 0) continue;
+    // A A^T over the lanes, P A^T over the columns of A as scalars
+    double aa[NR][NR];
+    {
+      double v[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = 0.0;
+#pragma unroll
+      for (int n = 0, i = 0; n < NR; ++n)
+#pragma unroll
+        for (int n2 = n; n2 < NR; ++n2, ++i) v[i] = av[n] * av[n2];
+      const double x = wave_sums(v, lane);
+#pragma unroll
+      for (int n = 0, i = 0; n < NR; ++n)
+#pragma unroll
+        for (int n2 = n; n2 < NR; ++n2, ++i) aa[n][n2] = aa[n2][n] = lane_value(x, 4 * i);
+    }
+    double gp[RP][NR][2];
+#pragma unroll
+    for (int u = 0; u < RP; ++u)
+#pragma unroll
+      for (int n = 0; n < NR; ++n) gp[u][n][0] = gp[u][n][1] = 0.0;
+#pragma unroll
+    for (int k = 0; k < G0; ++k) {
+#pragma unroll
+      for (int n = 0; n < NR; ++n) {
+        const double s = lane_value(av[n], k);
+#pragma unroll
+        for (int u = 0; u < RP; ++u) gp[u][n][k & 1] = fma((double)p[u][k], s, gp[u][n][k & 1]);
+      }
+      if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // the next columns of A wait: scalar registers
+    }
+#pragma unroll
+    for (int u = 0; u < RP; ++u)
+#pragma unroll
+      for (int n = 0; n < NR; ++n)
+        if (aa[n][n] > 0.0) {
+          double sg = 0.0;
+#pragma unroll
+          for (int n2 = 0; n2 < NR; ++n2) sg += f[u][n2] * aa[n2][n];
+          f[u][n] = row[u] ? fmax(0.0, f[u][n] + (gp[u][n][0] + gp[u][n][1] - sg) / aa[n][n]) : 0.0;
+        }
+  }
+#pragma unroll
+  for (int n = 0; n < NR; ++n) {
+#pragma unroll
+    for (int u = 0; u < RP; ++u)
+      if (row[u]) F[(t + 256 * u) * R8 + n] = f[u][n];
+    if (wv == 0 && col) A[lane * R8 + n] = av[n];
+  }
+  __syncthreads();
+}
+
 __device__ __forceinline__ void put_word(u64* p, unsigned tag, unsigned half) {
   __hip_atomic_store(p, ((u64)tag << 32) | half, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -182,7 +369,12 @@ __device__ __forceinline__ u64 get_word(u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
+// ROWS: every component is one workgroup's, few segments: half the threads,
+// with twice the registers, for the sweeps in registers (hals_rows)
+template <bool ROWS>
+__global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfSplit s) {
+  constexpr int CT = ROWS ? 512 : 1024, CW = CT / 64;
+  constexpr int CV = CT - 64;   // all waves but the last in the HALS product phases (the last: Gram)
   extern __shared__ double dyn[];
   __shared__ double red[CW];
   __shared__ int redi[CW];
@@ -211,7 +403,7 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
   // a component of one workgroup exchanges nothing: what it would put in its
   // slot goes to the LDS words where the totals are wanted (the caller's
   // barriers, or the thread itself, order the accesses)
-  const bool alone = nw == 1;
+  const bool alone = ROWS || nw == 1;
   // element j of this workgroup's slot for exchange e
   auto put = [&](unsigned e, size_t j, double v) {
     if (alone) {
@@ -344,7 +536,7 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
     LEAVE_IF_ABANDONED();
     double best;
     int j;
-    block_argmax(bv, bi, red, redi, &best, &j);
+    block_argmax<CW>(bv, bi, red, redi, &best, &j);
     if (best <= 0.0) break;
     if (N == 0) ref = best;
     else if (best < a.delta * ref) break;
@@ -383,7 +575,7 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
       const int col = picks[n];
       double mx = 0.0;
       for (int m = t; m < ml; m += CT) mx = fmax(mx, (double)Pl[m * Kp + col]);
-      mx = block_max(mx, red);
+      mx = block_max<CW>(mx, red);
       if (t == 0) put(ex, n, mx);
     }
     if (alone) __syncthreads();
@@ -584,7 +776,25 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
       return true;
     };
     bool ok = true;
-    switch (N) {
+    bool done = false;
+    if constexpr (ROWS) {
+      const int kc = (K + N + 15) / 16;
+      auto in_rows = [&](auto rank, auto per) {
+        constexpr int NR = decltype(rank)::value, RP = decltype(per)::value;
+        if (kc == 1) hals_rows<RP, NR, 1>(Pl, Kp, F, A, scr, ml, K, a.sweeps);
+        else if (kc == 2) hals_rows<RP, NR, 2>(Pl, Kp, F, A, scr, ml, K, a.sweeps);
+        else hals_rows<RP, NR, 3>(Pl, Kp, F, A, scr, ml, K, a.sweeps);
+      };
+      auto by_rank = [&](auto per) {
+        if (N == 1) in_rows(std::integral_constant<int, 1>{}, per);
+        else if (N == 2) in_rows(std::integral_constant<int, 2>{}, per);
+        else in_rows(std::integral_constant<int, 3>{}, per);
+      };
+      done = N <= 3 && rows_scratch(ml, K, N) <= s.scr;
+      if (done && ml <= 256) by_rank(std::integral_constant<int, 1>{});
+      else if (done) by_rank(std::integral_constant<int, 2>{});
+    }
+    if (!done) switch (N) {
       case 1: ok = hals(std::integral_constant<int, 1>{}); break;
       case 2: ok = hals(std::integral_constant<int, 2>{}); break;
       case 3: ok = hals(std::integral_constant<int, 3>{}); break;
@@ -600,7 +810,7 @@ __global__ __launch_bounds__(CT) void k_nmf_split(NmfArgs a, NmfSplit s) {
     for (int n = 0; n < N; ++n) {
       double mx = 0.0;
       for (int m = t; m < ml; m += CT) mx = fmax(mx, F[m * R8 + n]);
-      mx = block_max(mx, red);
+      mx = block_max<CW>(mx, red);
       if (t == 0) put(ex, n, mx);
     }
     double* peak = scr;
@@ -666,7 +876,14 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
   // launch costs about the same (its sweeps are latency bound), so the width
   // with the fewest launches wins.
   const bool few = K <= 96;
-  const int widths[] = {few ? 160 : 96, 128, few ? 96 : 160, 192, 64, 32};
+  // Short recordings whose components all fit one workgroup each take the
+  // sweeps in registers (0.25 ms against 0.86 at 8 segments, 0.20 against 0.90
+  // at 20, in registers first; 48 columns and the Gram entries are what the
+  // registers hold, and 512 rows of P_c and F what the LDS does).
+  int most = 0;
+  for (int k = 0; k < ncomp; ++k) most = std::max(most, coff[k + 1] - coff[k]);
+  const bool rows = K <= kRowsK && most <= kRowsMax;
+  const int widths[] = {rows ? (most + 63) / 64 * 64 : few ? 160 : 96, few ? 160 : 96, 128, few ? 96 : 160, 192, 64, 32};
   int best_mw = 0, best_groups = 0;
   for (const int mw : widths) {
     int scr = 0;
@@ -700,7 +917,9 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
   scr += (int)more;
   lds += 8 * more;
   int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_nmf_split, CT, lds) != hipSuccess || occ < 1)
+  s.rows = rows && mw >= most;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, s.rows ? k_nmf_split<true> : k_nmf_split<false>,
+                                                   s.rows ? 512 : 1024, lds) != hipSuccess || occ < 1)
     return false;
   s.mw = mw;
   s.Kp = K | 1;
@@ -782,6 +1001,13 @@ hipError_t launch_nmf_split(const NmfArgs& a, const NmfSplit& s, bool first, hip
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+  const void* kernel = reinterpret_cast<const void*>(s.rows ? k_nmf_split<true> : k_nmf_split<false>);
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds_bytes);
+  if (e != hipSuccess) return e;
+  if (s.rows) {   // nothing is exchanged
+    hipLaunchKernelGGL(k_nmf_split<true>, dim3(s.G), dim3(512), (unsigned)s.lds_bytes, st, a, s);
+    return hipGetLastError();
+  }
   {   // the slots of this launch carry no tag (tags start at 1)
     const long long words = (long long)s.G * 2 * 2 * s.XS * 2;   // 32-bit words
     if (words > INT_MAX) return hipErrorInvalidValue;
@@ -790,14 +1016,10 @@ hipError_t launch_nmf_split(const NmfArgs& a, const NmfSplit& s, bool first, hip
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_nmf_split),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds_bytes);
-  if (e != hipSuccess) return e;
   NmfArgs aa = a;
   NmfSplit ss = s;
   void* args[] = {&aa, &ss};
-  return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_nmf_split), dim3(s.G), dim3(CT), args,
-                                    (unsigned)s.lds_bytes, st);
+  return hipLaunchCooperativeKernel(kernel, dim3(s.G), dim3(1024), args, (unsigned)s.lds_bytes, st);
 }
 
 }  // namespace seg

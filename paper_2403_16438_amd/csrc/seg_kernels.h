@@ -102,6 +102,7 @@ hipError_t launch_nmf(const NmfArgs& a, hipStream_t st);
 struct NmfSplit {
   int G;                 // workgroups of one cooperative launch (all of them in the plan)
   int mw;                // pixels (rows of P_c) per workgroup
+  bool rows;             // every component is one workgroup's: sweeps in registers, nothing exchanged
   int Kp;                // LDS row stride of the P_c rows (odd)
   int scr;               // doubles of LDS scratch
   int XS;                // doubles per exchange slot

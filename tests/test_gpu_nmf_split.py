@@ -166,3 +166,42 @@ def test_component_sizes_of_every_exchange(K):
     assert np.array_equal(one["masks"], two["masks"])
     assert np.abs(one["weights"] - two["weights"]).max() <= 1e-5
     assert np.abs(one["activity"] - two["activity"]).max() <= 1e-5 * np.abs(one["activity"]).max()
+
+
+@pytest.mark.parametrize("K", [3, 13, 15, 29, 31, 44, 45])
+def test_sweeps_in_registers(K):
+    """Components of at most 512 pixels over at most 44 segments: one or two
+    rows per thread, ranks one to three and above, on both sides of every block
+    of 16 columns (and one segment more, which takes the other path): against
+    the one-workgroup-per-component kernel, to the bars of the comparison
+    above."""
+    rng = np.random.default_rng(10 * K)
+    H, W = 96, 160
+    yy, xx = np.mgrid[0:H, 0:W]
+    T = rng.uniform(0.5, 1.5, (K, H, W)).astype(np.float32)
+    discs = [(10, 10, 4), (14, 36, 9), (16, 70, 12), (50, 12, 6), (50, 19, 6), (50, 50, 6), (50, 57, 6), (56, 53, 6),
+             (50, 100, 5), (50, 107, 5), (57, 100, 5), (57, 107, 5), (50, 114, 5), (84, 30, 5), (84, 132, 9)]
+    for j, (cy, cx, r) in enumerate(discs):
+        d2 = (yy - cy) ** 2 + (xx - cx) ** 2
+        on = rng.random(K) < 0.3
+        on[j % K] = True
+        for i in np.flatnonzero(on):
+            T[i] += np.where(d2 <= r * r, rng.uniform(8, 14) * (1.3 - d2 / (r * r + 1.0)), 0.0).astype(np.float32)
+    D = np.full((K, H, W), 1.0 / np.sqrt(2 * np.pi), np.float32)
+    got = []
+    for path in (abi.SEG_NMF_SINGLE, abi.SEG_NMF_SPLIT):
+        s = Session(H, W, 50 * K, nmf_path=path, min_event_segs=1, area_max=4000)
+        s.load_summaries(T, np.ones_like(T), D)
+        s.finalize()
+        torch.cuda.synchronize()
+        assert s.profile()["nmf_path"] == path
+        sizes = np.bincount(s.image(abi.SEG_IMG_LABELS).ravel())[1:]
+        assert sizes.max() <= 512 and sizes.max() > 256 and sizes.min() <= 256
+        got.append(s.footprints())
+        s.close()
+    one, two = got
+    assert len(one["component"]) >= 6
+    assert np.array_equal(one["component"], two["component"])
+    assert np.array_equal(one["masks"], two["masks"])
+    assert np.abs(one["weights"] - two["weights"]).max() <= 1e-5
+    assert np.abs(one["activity"] - two["activity"]).max() <= 1e-5 * np.abs(one["activity"]).max()
