@@ -388,18 +388,27 @@ __global__ __launch_bounds__(256) void k_lin_dx(const uint16_t* __restrict__ W, 
   f32x16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll 4
-  for (int g = 0; g < K / 16; ++g) {
-    uint32_t aw[4], bw[4];
+  for (int k0 = 0; k0 < K; k0 += 64) {
+    uint16_t av[32];
+    float yv[32];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = 16 * g + 2 * q;
-      aw[q] = a[k * M] | (uint32_t)a[(k + 1) * M] << 16;
-      bw[q] = pk(y[(long long)k * N], y[(long long)(k + 1) * N]);
+    for (int e = 0; e < 32; ++e) {   // depth 16 (e / 8) + 8 h + e % 8 of the four steps
+      const int k = k0 + 16 * (e >> 3) + (e & 7);
+      av[e] = a[k * M];
+      yv[e] = y[(long long)k * N];
     }
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(aw[0], aw[1], aw[2], aw[3])),
-                                                  __builtin_bit_cast(bf16x8, make_uint4(bw[0], bw[1], bw[2], bw[3])),
-                                                  acc, 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      uint32_t aw[4], bw[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        aw[q] = av[8 * g + 2 * q] | (uint32_t)av[8 * g + 2 * q + 1] << 16;
+        bw[q] = pk(yv[8 * g + 2 * q], yv[8 * g + 2 * q + 1]);
+      }
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, make_uint4(aw[0], aw[1], aw[2], aw[3])),
+                                                    __builtin_bit_cast(bf16x8, make_uint4(bw[0], bw[1], bw[2], bw[3])),
+                                                    acc, 0, 0, 0);
+    }
   }
   if (n >= N) return;
 #pragma unroll

@@ -129,7 +129,7 @@ void to_bf16_copy(const float* w, uint16_t* wb, long long n, hipStream_t st);
 
 // ---- backward pass (k_nn_bwd.hip) ----
 // dX [M][N] = W^T dY for BF16 W [K][M] and dY [K][N]: M a multiple of 32, K of
-// 16, N below 2^31.
+// 64, N below 2^31.
 void lin_dx(const uint16_t* W, const float* dY, float* dX, int M, int K, long long N, hipStream_t st);
 // The temporal layers' input gradients: g2 [32][5][N] and g1 [32][10][N] from
 // the third layer's masked output gradient g3 [32][N] and the weights [32][160]
