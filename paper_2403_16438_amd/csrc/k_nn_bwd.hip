@@ -240,16 +240,17 @@ __global__ __launch_bounds__(DW_T) void k_dw3(const float* __restrict__ dY, cons
 // rows r; wave w computes row tile w, all waves load. 32 rows of dY take steps
 // of 512 columns with eight waves: the temporal layers' and the output layer's
 // gradients of 16 segments of 64 x 64, 190 us with 256 and four, take 147
-// (1,024 and sixteen are no faster).
-template <int RT, int KS, int NT>
+// (1,024 and sixteen are no faster). Only RB rows of X are staged: eight for
+// the first temporal layer's five (74 -> 61 us).
+template <int RT, int KS, int NT, int RB>
 __global__ __launch_bounds__(NT) void k_dw1(const float* __restrict__ dY, const float* __restrict__ X,
                                              float* __restrict__ P, int M, int R, int K, int kchunk, int Tin, int KT,
                                              int S, int Pd, int Np) {
   constexpr int G = KS / 8;
-  constexpr int AI = RT * 32 * G / NT, BI = 32 * G / NT;
-  static_assert(BI >= 1, "32 rows fill the workgroup");
+  constexpr int AI = RT * 32 * G / NT, BI = RB * G / NT;
+  static_assert(BI >= 1, "the rows fill the workgroup");
   __shared__ __attribute__((aligned(16))) uint16_t As[RT * 32][KS + 8];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[32][KS + 8];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[RB][KS + 8];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int r0 = blockIdx.y * 32, m0 = blockIdx.z * 32 * RT;
   const int kbeg = blockIdx.x * kchunk, kend = min(K, kbeg + kchunk);
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(NT) void k_dw1(const float* __restrict__ dY, const 
     if (k0 + KS < kend) load();
     if (wv < RT) {
       const uint16_t* a = &As[wv * 32 + (lane & 31)][(lane >> 5) * 8];
-      const uint16_t* b = &Bs[lane & 31][(lane >> 5) * 8];
+      const uint16_t* b = &Bs[RB == 32 ? lane & 31 : lane & (RB - 1)][(lane >> 5) * 8];
 #pragma unroll
       for (int ks = 0; ks < KS; ks += 16)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(a + ks),
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(256) void k_grad_reduce(GradTable t, float* __restr
 // neighbouring waves, so a second read of dY comes from the caches, and with no
 // barrier every load of four depth steps is in flight at once. Latency is what
 // bounds it (a few thousand columns, 8 or 16 steps): the two layers of a step of
-// 32 patches of 64 x 64 take 17 us; the tiled product, which waits for its
+// 32 patches of 64 x 64 take 13 us; the tiled product, which waits for its
 // loads at each of its steps, took 58.
 __global__ __launch_bounds__(256) void k_lin_dx(const uint16_t* __restrict__ W, const float* __restrict__ dY,
                                                 float* __restrict__ dX, int M, int K, int N) {
@@ -673,13 +674,15 @@ bool dw1(const float* dY, const float* X, float* P, int M, int R, long long K, i
          long long Np, hipStream_t st) {
   if (Np % 8 || K % 8 || K > 0x3fffffffLL || ((uintptr_t)dY & 15) || ((uintptr_t)X & 15)) return false;
   const int kc = grad_chunk(K), z = grad_ranges(K), rb = (R + 31) / 32;
-#define DW1(RT, KS, NT)                                                                                           \
-  hipLaunchKernelGGL((k_dw1<RT, KS, NT>), dim3(z, rb, (M + 32 * RT - 1) / (32 * RT)), dim3(NT), 0, st, dY, X, P, M, R, \
-                     (int)K, kc, Tin, KT, S, Pd, (int)Np)
-  if (M <= 32)
-    DW1(1, 512, 512);
+#define DW1(RT, KS, NT, RB)                                                                                          \
+  hipLaunchKernelGGL((k_dw1<RT, KS, NT, RB>), dim3(z, rb, (M + 32 * RT - 1) / (32 * RT)), dim3(NT), 0, st, dY, X, P, M, \
+                     R, (int)K, kc, Tin, KT, S, Pd, (int)Np)
+  if (M <= 32 && R <= 8)
+    DW1(1, 512, 512, 8);
+  else if (M <= 32)
+    DW1(1, 512, 512, 32);
   else
-    DW1(2, 128, 256);
+    DW1(2, 128, 256, 32);
 #undef DW1
   return true;
 }
