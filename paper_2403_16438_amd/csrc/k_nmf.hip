@@ -437,4 +437,30 @@ hipError_t launch_nmf(const NmfArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+namespace {
+// Several ranges of 32-bit words into one, in one launch: five copies by the
+// runtime took 4 to 5 us each.
+__global__ __launch_bounds__(256) void k_pack(PackArgs p) {
+  const uint32_t* src = nullptr;
+  uint32_t j = blockIdx.x * 256 + threadIdx.x, at = 0;
+  for (int k = 0; k < p.n; ++k) {
+    if (j < p.words[k]) {
+      src = p.src[k];
+      at = p.at[k];
+      break;
+    }
+    j -= p.words[k];
+  }
+  if (src) p.dst[at + j] = src[j];
+}
+}  // namespace
+
+hipError_t launch_pack(const PackArgs& p, hipStream_t st) {
+  uint64_t total = 0;
+  for (int k = 0; k < p.n; ++k) total += p.words[k];
+  if (total > 0xffffff00ULL) return hipErrorInvalidValue;
+  if (total) hipLaunchKernelGGL(k_pack, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, p);
+  return hipGetLastError();
+}
+
 }  // namespace seg

@@ -185,7 +185,7 @@ using u64 = unsigned long long;
 // the same A and takes its columns as scalars for the rows of P A^T. What
 // bounds it is the instructions of one wave per SIMD, the divisions' chains
 // among them. The NMF of a 64 x 64 x 1,000 recording (three components of 200
-// to 300 pixels, rank 1, 200 sweeps) takes 0.20 ms; with P_c in LDS, five
+// to 300 pixels, rank 1, 200 sweeps) takes 0.32 ms; with P_c in LDS, five
 // barriers a sweep and an exchange of slots between two workgroups it took
 // 0.90. At rank 2 and 370 pixels 0.75 against 1.14 ms (all eight waves with one
 // row each: 1.00; 1,024 threads and so half the registers: 1.07).
@@ -877,7 +877,7 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
   // with the fewest launches wins.
   const bool few = K <= 96;
   // Short recordings whose components all fit one workgroup each take the
-  // sweeps in registers (0.25 ms against 0.86 at 8 segments, 0.20 against 0.90
+  // sweeps in registers (0.25 ms against 0.86 at 8 segments, 0.32 against 0.90
   // at 20, in registers first; 48 columns and the Gram entries are what the
   // registers hold, and 512 rows of P_c and F what the LDS does).
   int most = 0;

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -548,43 +549,46 @@ int seg_finalize(seg_session* s, void* stream) {
     }
     if ((e = fail(s, hipEventRecord(s->ev[3], st)))) return e;
     nmf_timed = true;
-    const size_t npx = pix.size();
-    std::vector<int> N(ncomp);
-    std::vector<double> F(npx * seg::kMaxRank), A((size_t)ncomp * seg::kMaxRank * s->Kmax);
+    const size_t npx = pix.size(), nF = npx * seg::kMaxRank, nA = (size_t)ncomp * seg::kMaxRank * s->Kmax;
     unsigned split_error = 0;
-    // The results (error flag, ranks, pixel lists, F, A) are packed by
-    // device-to-device copies into the P_c area, free after the NMF, and come
-    // back in one copy: each copy into pageable host memory waits for the
-    // device, so five of them cost five round trips.
+    // The results (error flag, ranks, pixel lists, F, A) are packed into the
+    // P_c area, free after the NMF, and come back in one copy (each copy into
+    // pageable host memory waits for the device), into memory that nothing
+    // fills before and from which they are read in place.
     const size_t o_err = 0, o_n = 8, o_pix = seg::align_up(o_n + (size_t)ncomp * 4),
-                 o_f = seg::align_up(o_pix + npx * 4), o_a = o_f + F.size() * 8, packed = o_a + A.size() * 8;
-    if (packed <= (size_t)s->M * s->Kmax * 8) {
-      char* dst = reinterpret_cast<char*>(na.P);
-      hipError_t he = hipSuccess;
-      if (split) he = hipMemcpyAsync(dst + o_err, sp.sync + ncomp, 4, hipMemcpyDeviceToDevice, st);
-      if (he == hipSuccess) he = hipMemcpyAsync(dst + o_n, na.N, (size_t)ncomp * 4, hipMemcpyDeviceToDevice, st);
-      if (he == hipSuccess) he = hipMemcpyAsync(dst + o_pix, dpix, npx * 4, hipMemcpyDeviceToDevice, st);
-      if (he == hipSuccess) he = hipMemcpyAsync(dst + o_f, na.F, F.size() * 8, hipMemcpyDeviceToDevice, st);
-      if (he == hipSuccess) he = hipMemcpyAsync(dst + o_a, na.A, A.size() * 8, hipMemcpyDeviceToDevice, st);
-      std::vector<double> host((packed + 7) / 8);
-      if (he == hipSuccess) he = hipMemcpyAsync(host.data(), dst, packed, hipMemcpyDeviceToHost, st);
-      if (he == hipSuccess) he = hipStreamSynchronize(st);
-      if ((e = fail(s, he))) return e;
-      const char* h = reinterpret_cast<const char*>(host.data());
-      if (split) std::memcpy(&split_error, h + o_err, 4);
-      std::memcpy(N.data(), h + o_n, (size_t)ncomp * 4);
-      std::memcpy(pix.data(), h + o_pix, npx * 4);
-      std::memcpy(F.data(), h + o_f, F.size() * 8);
-      std::memcpy(A.data(), h + o_a, A.size() * 8);
+                 o_f = seg::align_up(o_pix + npx * 4), o_a = o_f + nF * 8, packed = o_a + nA * 8;
+    std::unique_ptr<char[]> host(new (std::nothrow) char[packed]);
+    if (!host) return fail(s, hipErrorOutOfMemory);
+    char* h = host.get();
+    const int* N = reinterpret_cast<const int*>(h + o_n);
+    const double* F = reinterpret_cast<const double*>(h + o_f);
+    const double* A = reinterpret_cast<const double*>(h + o_a);
+    const struct { const void* from; size_t at, bytes; } part[5] = {{na.N, o_n, (size_t)ncomp * 4},
+                                                                    {dpix, o_pix, npx * 4},
+                                                                    {na.F, o_f, nF * 8},
+                                                                    {na.A, o_a, nA * 8},
+                                                                    {split ? sp.sync + ncomp : nullptr, o_err, 4}};
+    const int parts = split ? 5 : 4;
+    hipError_t he = hipSuccess;
+    if (packed <= (size_t)s->M * s->Kmax * 8 && packed / 4 < 0xffffff00ULL) {
+      seg::PackArgs pk{};
+      pk.n = parts;
+      pk.dst = reinterpret_cast<uint32_t*>(na.P);
+      for (int k = 0; k < parts; ++k) {
+        pk.src[k] = static_cast<const uint32_t*>(part[k].from);
+        pk.words[k] = (uint32_t)(part[k].bytes / 4);
+        pk.at[k] = (uint32_t)(part[k].at / 4);
+      }
+      he = seg::launch_pack(pk, st);
+      if (he == hipSuccess) he = hipMemcpyAsync(h, na.P, packed, hipMemcpyDeviceToHost, st);
     } else {
-      if ((e = fail(s, hipMemcpyAsync(N.data(), na.N, ncomp * 4, hipMemcpyDeviceToHost, st)))) return e;
-      if ((e = fail(s, hipMemcpyAsync(pix.data(), dpix, pix.size() * 4, hipMemcpyDeviceToHost, st)))) return e;
-      if ((e = fail(s, hipMemcpyAsync(F.data(), na.F, F.size() * 8, hipMemcpyDeviceToHost, st)))) return e;
-      if ((e = fail(s, hipMemcpyAsync(A.data(), na.A, A.size() * 8, hipMemcpyDeviceToHost, st)))) return e;
-      if (split && (e = fail(s, hipMemcpyAsync(&split_error, sp.sync + ncomp, 4, hipMemcpyDeviceToHost, st))))
-        return e;
-      if ((e = fail(s, hipStreamSynchronize(st)))) return e;
+      for (int k = 0; k < parts && he == hipSuccess; ++k)
+        he = hipMemcpyAsync(h + part[k].at, part[k].from, part[k].bytes, hipMemcpyDeviceToHost, st);
     }
+    if (he == hipSuccess) he = hipStreamSynchronize(st);
+    if ((e = fail(s, he))) return e;
+    if (split) std::memcpy(&split_error, h + o_err, 4);
+    std::memcpy(pix.data(), h + o_pix, npx * 4);
     if (hold.owns_lock()) hold.unlock();
     if (split_error) return fail(s, hipErrorLaunchTimeOut);  // a wait for a slot was abandoned
     // algorithmic work of the NMF (seg_profile)

@@ -130,4 +130,13 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
 // slots first; `first` also clears the abandon and error flags.
 hipError_t launch_nmf_split(const NmfArgs& a, const NmfSplit& s, bool first, hipStream_t st);
 
+// n ranges of 32-bit words, range k to dst + at[k]
+struct PackArgs {
+  int n;
+  const uint32_t* src[5];
+  uint32_t words[5], at[5];
+  uint32_t* dst;
+};
+hipError_t launch_pack(const PackArgs& p, hipStream_t st);
+
 }  // namespace seg
