@@ -1533,16 +1533,20 @@ __global__ void k_to_bf16(const float* __restrict__ w, uint16_t* __restrict__ wb
 
 // ---- summary-image input (S, T) -------------------------------------------
 
-// One 1024-thread block per patch (the FP64 divisions and square roots of
-// the pixels are the work): exact-enough FP64 mean and population deviation
-// of S, then channel 0 = (S - mean) / max(sd, 1e-3), channel 1 = T / sqrt(S + 25).
-constexpr int NORM_NT = 1024;
+// FP64 mean and population deviation of S, then channel 0 = (S - mean) /
+// max(sd, 1e-3), channel 1 = T / sqrt(S + 25). The FP64 divisions and square
+// roots of the pixels are the work: NORM_Q blocks of 1,024 threads per patch
+// each form the patch's sums (alike, in one order) and normalise their part of
+// its pixels (49 patches of 64 x 64: 7.2 us with one block per patch,
+// 5.8 with four).
+constexpr int NORM_NT = 1024, NORM_Q = 4;
 __global__ __launch_bounds__(NORM_NT) void k_st_norm(const float* __restrict__ stin, float* __restrict__ x, int Bn,
                                                      long long HW) {
   const int b = blockIdx.x, tid = threadIdx.x;
   const float* S = stin + (size_t)b * 2 * HW;
   const float* T = S + HW;
   double s = 0.0, s2 = 0.0;
+#pragma unroll 4
   for (long long i = tid; i < HW; i += NORM_NT) {
     const double v = S[i];
     s += v;
@@ -1552,16 +1556,24 @@ __global__ __launch_bounds__(NORM_NT) void k_st_norm(const float* __restrict__ s
   r1[tid] = s;
   r2[tid] = s2;
   __syncthreads();
-  for (int o = NORM_NT / 2; o > 0; o >>= 1) {
+  for (int o = NORM_NT / 2; o >= 64; o >>= 1) {
     if (tid < o) {
       r1[tid] += r1[tid + o];
       r2[tid] += r2[tid + o];
     }
     __syncthreads();
   }
-  const double m = r1[0] / (double)HW;
-  const double sd = fmax(sqrt(fmax(r2[0] / (double)HW - m * m, 0.0)), 1e-3);
-  for (long long i = tid; i < HW; i += NORM_NT) {
+  // every wave ends the sums itself, from the same 64 values
+  s = r1[tid & 63];
+  s2 = r2[tid & 63];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    s += __shfl_down(s, o, 64);
+    s2 += __shfl_down(s2, o, 64);
+  }
+  const double m = __shfl(s, 0, 64) / (double)HW;
+  const double sd = fmax(sqrt(fmax(__shfl(s2, 0, 64) / (double)HW - m * m, 0.0)), 1e-3);
+  for (long long i = (long long)blockIdx.y * NORM_NT + tid; i < HW; i += NORM_NT * NORM_Q) {
     x[(size_t)b * HW + i] = (float)(((double)S[i] - m) / sd);
     x[((size_t)Bn + b) * HW + i] = (float)((double)T[i] / sqrt(fmax((double)S[i], 0.0) + 25.0));
   }
@@ -1863,7 +1875,7 @@ void rmsprop(float* w, const float* g, float* v, uint16_t* wb, long long n, floa
 void to_bf16_copy(const float* w, uint16_t* wb, long long n, hipStream_t st) { L1(k_to_bf16, n, w, wb, n); }
 
 void st_norm(const float* stin, float* x, int Bn, long long HW, hipStream_t stream) {
-  hipLaunchKernelGGL(k_st_norm, dim3((unsigned)Bn), dim3(NORM_NT), 0, stream, stin, x, Bn, HW);
+  hipLaunchKernelGGL(k_st_norm, dim3((unsigned)Bn, NORM_Q), dim3(NORM_NT), 0, stream, stin, x, Bn, HW);
 }
 int st_origins(int n) { return (n - 64 + 31) / 32 + 1; }
 void st_patches(const float* S, const float* T, int H, int W, float* out, hipStream_t st) {
