@@ -495,6 +495,9 @@ def main():
                "algorithmic_bytes_per_launch": bytes_alg,
                "hbm_algorithmic_GBps": bytes_alg / seconds / 1e9,
                "hbm_frac": bytes_alg / seconds / HBM_PEAK}
+        if kernel == "k_block_stats":
+            out["note"] = ("the algorithm's operations (two 25-tap passes) against the FP64 peak; the kernel forms "
+                           "them as exact byte products on INT8 MFMA")
         return out
 
     # voltage traces (the stage after segmentation) of the resident video,
@@ -554,7 +557,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "u16 in, f64 smoothing, f32 summaries",
+        "dtype": "u16 in, fixed-point smoothing (int8 products, int32 and f64 sums), f32 summaries",
         "data": "synthetic (seeded simulator: 30 neurons, Poisson-Gaussian noise)",
         "config": {"workload": f"{H}x{W}x{T} uint16 video, 741 fps, seed {args.seed}, "
                                "whole video pushed then finalized",
