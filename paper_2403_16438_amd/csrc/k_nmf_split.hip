@@ -188,8 +188,11 @@ using u64 = unsigned long long;
 // to 300 pixels, rank 1, 200 sweeps) takes 0.32 ms; with P_c in LDS, five
 // barriers a sweep and an exchange of slots between two workgroups it took
 // 0.90. At rank 2 and 370 pixels 0.75 against 1.14 ms (all eight waves with one
-// row each: 1.00; 1,024 threads and so half the registers: 1.07).
-constexpr int kRowsMax = 512, kRowsK = 44;   // and rank at most 3
+// row each: 1.00; 1,024 threads and so half the registers: 1.07). A component
+// whose rank turns out to be higher (the plan is made before the projections
+// find it) is left, marked by kNmfLeft in place of its rank, for the launch
+// that splits components.
+constexpr int kRowsMax = 512, kRowsK = 44, kRowsRank = 3;
 
 __device__ __forceinline__ double swap_add32(double a, double b) {
   const u64 x = (u64)__double_as_longlong(a), y = (u64)__double_as_longlong(b);
@@ -236,9 +239,7 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 }
 
 // doubles of LDS: two sets of the waves' sums
-__device__ __forceinline__ int rows_scratch(int ml, int K, int N) {
-  return 2 * min(4, (ml + 63) / 64) * N * ((K + N + 15) / 16 * 16);
-}
+constexpr int rows_scratch(int K) { return 2 * 4 * kRowsRank * ((K + kRowsRank + 15) / 16 * 16); }
 
 // RP rows per thread of the first four waves, NR rank, KC blocks of 16
 // columns: K columns of P_c, and in the last NR the entries (n, n2) of F^T F,
@@ -540,6 +541,10 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
     if (best <= 0.0) break;
     if (N == 0) ref = best;
     else if (best < a.delta * ref) break;
+    if (ROWS && N == kRowsRank) {
+      if (t == 0) a.N[c] = kNmfLeft;
+      return;
+    }
     if (t == 0) picks[N] = j;
     ++N;
     for (int m = t; m < ml; m += CT) U[m] = R[(long long)m * K + j] / best;
@@ -591,192 +596,6 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
     for (int e = t; e < K * R8; e += CT) A[e] = 0.0;
     LEAVE_IF_ABANDONED();
 
-    // HALS, compiled per rank so that the sequential row/column updates run
-    // without predication
-    auto hals = [&](auto rank) -> bool {
-      constexpr int NR = decltype(rank)::value;
-      constexpr int NP = NR * (NR + 1) / 2;
-      for (int sweep = -1; sweep < a.sweeps; ++sweep) {
-        // ---- partial F^T P and F^T F over own rows (FP64, fixed order),
-        // written to this workgroup's slot. Waves 0..14: thread (row chunk
-        // q, segment i) sums its rows for all NR columns of F; after the
-        // barrier the chunks are added in order and written to the slot,
-        // and the gather of the totals follows without another barrier.
-        // Wave 15: F^T F, whole within the wave (gram_wave), straight to the
-        // slot.
-        {
-          // chunks of about 16 rows, at least 8 and at most 24 of them
-          const int QC = max(1, min(min(CV / K, max(8, min(24, ml / 16))), s.scr / (K * NR)));
-          const int rows = (ml + QC - 1) / QC;
-          if (t < CV) {
-            for (int e = t; e < QC * K; e += CV) {
-              const int q = e / K, i = e - q * K;
-              const int m1 = min(ml, (q + 1) * rows);
-              double s0[NR], s1[NR];
-#pragma unroll
-              for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
-              int m = q * rows;
-              if constexpr (NR <= 3) {   // four rows' reads in flight
-                for (; m + 3 < m1; m += 4) {
-                  double p[4], f[4][NR];
-#pragma unroll
-                  for (int u = 0; u < 4; ++u) {
-                    p[u] = (double)Pl[(m + u) * Kp + i];
-#pragma unroll
-                    for (int n = 0; n < NR; ++n) f[u][n] = F[(m + u) * R8 + n];
-                  }
-#pragma unroll
-                  for (int n = 0; n < NR; ++n) {
-                    s0[n] = fma(f[0][n], p[0], s0[n]);
-                    s1[n] = fma(f[1][n], p[1], s1[n]);
-                    s0[n] = fma(f[2][n], p[2], s0[n]);
-                    s1[n] = fma(f[3][n], p[3], s1[n]);
-                  }
-                }
-              }
-              for (; m + 1 < m1; m += 2) {
-                const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[(m + 1) * Kp + i];
-#pragma unroll
-                for (int n = 0; n < NR; ++n) {
-                  s0[n] = fma(F[m * R8 + n], p0, s0[n]);
-                  s1[n] = fma(F[(m + 1) * R8 + n], p1, s1[n]);
-                }
-              }
-              if (m < m1) {
-                const double p0 = (double)Pl[m * Kp + i];
-#pragma unroll
-                for (int n = 0; n < NR; ++n) s0[n] = fma(F[m * R8 + n], p0, s0[n]);
-              }
-#pragma unroll
-              for (int n = 0; n < NR; ++n) {
-                if (QC == 1) put(ex, (size_t)n * K + i, s0[n] + s1[n]);
-                else scr[(size_t)e * NR + n] = s0[n] + s1[n];
-              }
-            }
-          } else {   // F^T F of the own rows, upper triangle
-            const double v = gram_wave<NR>(F, ml, t - CV, gpart);
-            if (t - CV < NP) {
-              int n1, n2;
-              pair_of<NR>(t - CV, n1, n2);
-              put(ex, (size_t)R8 * K + n1 * R8 + n2, v);
-            }
-          }
-          __syncthreads();
-          if (QC > 1)
-            for (int o = t; o < NR * K; o += CT) {
-              const int n = o / K, i = o - n * K;
-              put(ex, o, chunk_sum(scr + (size_t)i * NR + n, (size_t)K * NR, QC));
-            }
-        }
-        // ---- totals over the component's workgroups (slot order) into LDS:
-        // the NR K entries of F^T P, then the upper triangle of F^T F (mirrored)
-        for (int e = t; e < NR * K + NP; e += CT) {
-          if (e < NR * K) {
-            if (!alone) FtP[e] = gather(e, ex, false);
-          } else {
-            int n1, n2;
-            pair_of<NR>(e - NR * K, n1, n2);
-            const double v = gather((unsigned)(R8 * K + n1 * R8 + n2), ex, false);
-            gF[n1 * R8 + n2] = v;
-            gF[n2 * R8 + n1] = v;
-          }
-        }
-        ++ex;
-        LEAVE_IF_ABANDONED(false);
-        // ---- the A update (rows of A in order), every workgroup alike
-        for (int i = t; i < K; i += CT) {
-          double av[NR];
-#pragma unroll
-          for (int n = 0; n < NR; ++n) av[n] = A[i * R8 + n];
-#pragma unroll
-          for (int n = 0; n < NR; ++n) {
-            // from rank 6 on, hoisting all Gram reads would spill: keep them per row
-            if constexpr (NR > 5) asm volatile("" ::: "memory");
-            const double d = gF[n * R8 + n];
-            if (d > 0.0) {
-              double sg = 0.0;
-#pragma unroll
-              for (int n2 = 0; n2 < NR; ++n2) sg += gF[n * R8 + n2] * av[n2];
-              av[n] = fmax(0.0, av[n] + (FtP[n * K + i] - sg) / d);
-            }
-          }
-#pragma unroll
-          for (int n = 0; n < NR; ++n) A[i * R8 + n] = av[n];
-        }
-        __syncthreads();
-        if (sweep < 0) continue;
-        // ---- P A^T of own rows and A A^T (FP64, fixed order). Waves
-        // 0..14: thread (segment chunk q, own row m) sums its segments for
-        // all NR rows of A. Wave 15: A A^T whole within the wave, chunked by
-        // K and NR only, so identical in every workgroup.
-        // at most 16 chunks: their in-order sum is a chain of dependent adds
-        const int QK = max(1, min(min(CV / ml, 16), s.scr / (ml * NR)));
-        {
-          const int seg = (K + QK - 1) / QK;
-          if (t < CV) {
-            for (int e = t; e < QK * ml; e += CV) {
-              const int q = e / ml, m = e - q * ml;
-              const int i1 = min(K, (q + 1) * seg);
-              double s0[NR], s1[NR];
-#pragma unroll
-              for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
-              int i = q * seg;
-              for (; i + 1 < i1; i += 2) {
-                const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[m * Kp + i + 1];
-#pragma unroll
-                for (int n = 0; n < NR; ++n) {
-                  s0[n] = fma(p0, A[i * R8 + n], s0[n]);
-                  s1[n] = fma(p1, A[(i + 1) * R8 + n], s1[n]);
-                }
-              }
-              if (i < i1) {
-                const double p0 = (double)Pl[m * Kp + i];
-#pragma unroll
-                for (int n = 0; n < NR; ++n) s0[n] = fma(p0, A[i * R8 + n], s0[n]);
-              }
-#pragma unroll
-              for (int n = 0; n < NR; ++n) scr[(size_t)e * NR + n] = s0[n] + s1[n];
-            }
-          } else {   // A A^T, upper triangle mirrored (every workgroup alike)
-            const double v = gram_wave<NR>(A, K, t - CV, gpart);
-            if (t - CV < NP) {
-              int n1, n2;
-              pair_of<NR>(t - CV, n1, n2);
-              gA[n1 * R8 + n2] = v;
-              gA[n2 * R8 + n1] = v;
-            }
-          }
-          __syncthreads();
-        }
-        // ---- the own F rows (columns of F in order), each thread adding
-        // its row's P A^T chunks in order first
-        for (int m = t; m < ml; m += CT) {
-          double gp[NR], f[NR];
-#pragma unroll
-          for (int n = 0; n < NR; ++n) {
-            gp[n] = chunk_sum(scr + (size_t)m * NR + n, (size_t)ml * NR, QK);   // P A^T: chunks in order
-            f[n] = F[m * R8 + n];
-          }
-#pragma unroll
-          for (int n = 0; n < NR; ++n) {
-            if constexpr (NR > 5) asm volatile("" ::: "memory");
-            const double d = gA[n * R8 + n];
-            if (d > 0.0) {
-              double sg = 0.0;
-#pragma unroll
-              for (int n2 = 0; n2 < NR; ++n2) sg += f[n2] * gA[n2 * R8 + n];
-              f[n] = fmax(0.0, f[n] + (gp[n] - sg) / d);
-            }
-          }
-#pragma unroll
-          for (int n = 0; n < NR; ++n) F[m * R8 + n] = f[n];
-        }
-        __syncthreads();
-      }
-      return true;
-    };
-    bool ok = true;
-    bool done = false;
     if constexpr (ROWS) {
       const int kc = (K + N + 15) / 16;
       auto in_rows = [&](auto rank, auto per) {
@@ -790,21 +609,206 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
         else if (N == 2) in_rows(std::integral_constant<int, 2>{}, per);
         else in_rows(std::integral_constant<int, 3>{}, per);
       };
-      done = N <= 3 && rows_scratch(ml, K, N) <= s.scr;
-      if (done && ml <= 256) by_rank(std::integral_constant<int, 1>{});
-      else if (done) by_rank(std::integral_constant<int, 2>{});
+      if (ml <= 256) by_rank(std::integral_constant<int, 1>{});
+      else by_rank(std::integral_constant<int, 2>{});
+    } else {
+      // HALS, compiled per rank so that the sequential row/column updates run
+      // without predication
+      auto hals = [&](auto rank) -> bool {
+        constexpr int NR = decltype(rank)::value;
+        constexpr int NP = NR * (NR + 1) / 2;
+        for (int sweep = -1; sweep < a.sweeps; ++sweep) {
+          // ---- partial F^T P and F^T F over own rows (FP64, fixed order),
+          // written to this workgroup's slot. Waves 0..14: thread (row chunk
+          // q, segment i) sums its rows for all NR columns of F; after the
+          // barrier the chunks are added in order and written to the slot,
+          // and the gather of the totals follows without another barrier.
+          // Wave 15: F^T F, whole within the wave (gram_wave), straight to the
+          // slot.
+          {
+            // chunks of about 16 rows, at least 8 and at most 24 of them
+            const int QC = max(1, min(min(CV / K, max(8, min(24, ml / 16))), s.scr / (K * NR)));
+            const int rows = (ml + QC - 1) / QC;
+            if (t < CV) {
+              for (int e = t; e < QC * K; e += CV) {
+                const int q = e / K, i = e - q * K;
+                const int m1 = min(ml, (q + 1) * rows);
+                double s0[NR], s1[NR];
+  #pragma unroll
+                for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
+                int m = q * rows;
+                if constexpr (NR <= 3) {   // four rows' reads in flight
+                  for (; m + 3 < m1; m += 4) {
+                    double p[4], f[4][NR];
+  #pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                      p[u] = (double)Pl[(m + u) * Kp + i];
+  #pragma unroll
+                      for (int n = 0; n < NR; ++n) f[u][n] = F[(m + u) * R8 + n];
+                    }
+  #pragma unroll
+                    for (int n = 0; n < NR; ++n) {
+                      s0[n] = fma(f[0][n], p[0], s0[n]);
+                      s1[n] = fma(f[1][n], p[1], s1[n]);
+                      s0[n] = fma(f[2][n], p[2], s0[n]);
+                      s1[n] = fma(f[3][n], p[3], s1[n]);
+                    }
+                  }
+                }
+                for (; m + 1 < m1; m += 2) {
+                  const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[(m + 1) * Kp + i];
+  #pragma unroll
+                  for (int n = 0; n < NR; ++n) {
+                    s0[n] = fma(F[m * R8 + n], p0, s0[n]);
+                    s1[n] = fma(F[(m + 1) * R8 + n], p1, s1[n]);
+                  }
+                }
+                if (m < m1) {
+                  const double p0 = (double)Pl[m * Kp + i];
+  #pragma unroll
+                  for (int n = 0; n < NR; ++n) s0[n] = fma(F[m * R8 + n], p0, s0[n]);
+                }
+  #pragma unroll
+                for (int n = 0; n < NR; ++n) {
+                  if (QC == 1) put(ex, (size_t)n * K + i, s0[n] + s1[n]);
+                  else scr[(size_t)e * NR + n] = s0[n] + s1[n];
+                }
+              }
+            } else {   // F^T F of the own rows, upper triangle
+              const double v = gram_wave<NR>(F, ml, t - CV, gpart);
+              if (t - CV < NP) {
+                int n1, n2;
+                pair_of<NR>(t - CV, n1, n2);
+                put(ex, (size_t)R8 * K + n1 * R8 + n2, v);
+              }
+            }
+            __syncthreads();
+            if (QC > 1)
+              for (int o = t; o < NR * K; o += CT) {
+                const int n = o / K, i = o - n * K;
+                put(ex, o, chunk_sum(scr + (size_t)i * NR + n, (size_t)K * NR, QC));
+              }
+          }
+          // ---- totals over the component's workgroups (slot order) into LDS:
+          // the NR K entries of F^T P, then the upper triangle of F^T F (mirrored)
+          for (int e = t; e < NR * K + NP; e += CT) {
+            if (e < NR * K) {
+              if (!alone) FtP[e] = gather(e, ex, false);
+            } else {
+              int n1, n2;
+              pair_of<NR>(e - NR * K, n1, n2);
+              const double v = gather((unsigned)(R8 * K + n1 * R8 + n2), ex, false);
+              gF[n1 * R8 + n2] = v;
+              gF[n2 * R8 + n1] = v;
+            }
+          }
+          ++ex;
+          LEAVE_IF_ABANDONED(false);
+          // ---- the A update (rows of A in order), every workgroup alike
+          for (int i = t; i < K; i += CT) {
+            double av[NR];
+  #pragma unroll
+            for (int n = 0; n < NR; ++n) av[n] = A[i * R8 + n];
+  #pragma unroll
+            for (int n = 0; n < NR; ++n) {
+              // from rank 6 on, hoisting all Gram reads would spill: keep them per row
+              if constexpr (NR > 5) asm volatile("" ::: "memory");
+              const double d = gF[n * R8 + n];
+              if (d > 0.0) {
+                double sg = 0.0;
+  #pragma unroll
+                for (int n2 = 0; n2 < NR; ++n2) sg += gF[n * R8 + n2] * av[n2];
+                av[n] = fmax(0.0, av[n] + (FtP[n * K + i] - sg) / d);
+              }
+            }
+  #pragma unroll
+            for (int n = 0; n < NR; ++n) A[i * R8 + n] = av[n];
+          }
+          __syncthreads();
+          if (sweep < 0) continue;
+          // ---- P A^T of own rows and A A^T (FP64, fixed order). Waves
+          // 0..14: thread (segment chunk q, own row m) sums its segments for
+          // all NR rows of A. Wave 15: A A^T whole within the wave, chunked by
+          // K and NR only, so identical in every workgroup.
+          // at most 16 chunks: their in-order sum is a chain of dependent adds
+          const int QK = max(1, min(min(CV / ml, 16), s.scr / (ml * NR)));
+          {
+            const int seg = (K + QK - 1) / QK;
+            if (t < CV) {
+              for (int e = t; e < QK * ml; e += CV) {
+                const int q = e / ml, m = e - q * ml;
+                const int i1 = min(K, (q + 1) * seg);
+                double s0[NR], s1[NR];
+  #pragma unroll
+                for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
+                int i = q * seg;
+                for (; i + 1 < i1; i += 2) {
+                  const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[m * Kp + i + 1];
+  #pragma unroll
+                  for (int n = 0; n < NR; ++n) {
+                    s0[n] = fma(p0, A[i * R8 + n], s0[n]);
+                    s1[n] = fma(p1, A[(i + 1) * R8 + n], s1[n]);
+                  }
+                }
+                if (i < i1) {
+                  const double p0 = (double)Pl[m * Kp + i];
+  #pragma unroll
+                  for (int n = 0; n < NR; ++n) s0[n] = fma(p0, A[i * R8 + n], s0[n]);
+                }
+  #pragma unroll
+                for (int n = 0; n < NR; ++n) scr[(size_t)e * NR + n] = s0[n] + s1[n];
+              }
+            } else {   // A A^T, upper triangle mirrored (every workgroup alike)
+              const double v = gram_wave<NR>(A, K, t - CV, gpart);
+              if (t - CV < NP) {
+                int n1, n2;
+                pair_of<NR>(t - CV, n1, n2);
+                gA[n1 * R8 + n2] = v;
+                gA[n2 * R8 + n1] = v;
+              }
+            }
+            __syncthreads();
+          }
+          // ---- the own F rows (columns of F in order), each thread adding
+          // its row's P A^T chunks in order first
+          for (int m = t; m < ml; m += CT) {
+            double gp[NR], f[NR];
+  #pragma unroll
+            for (int n = 0; n < NR; ++n) {
+              gp[n] = chunk_sum(scr + (size_t)m * NR + n, (size_t)ml * NR, QK);   // P A^T: chunks in order
+              f[n] = F[m * R8 + n];
+            }
+  #pragma unroll
+            for (int n = 0; n < NR; ++n) {
+              if constexpr (NR > 5) asm volatile("" ::: "memory");
+              const double d = gA[n * R8 + n];
+              if (d > 0.0) {
+                double sg = 0.0;
+  #pragma unroll
+                for (int n2 = 0; n2 < NR; ++n2) sg += f[n2] * gA[n2 * R8 + n];
+                f[n] = fmax(0.0, f[n] + (gp[n] - sg) / d);
+              }
+            }
+  #pragma unroll
+            for (int n = 0; n < NR; ++n) F[m * R8 + n] = f[n];
+          }
+          __syncthreads();
+        }
+        return true;
+      };
+      bool ok = true;
+      switch (N) {
+        case 1: ok = hals(std::integral_constant<int, 1>{}); break;
+        case 2: ok = hals(std::integral_constant<int, 2>{}); break;
+        case 3: ok = hals(std::integral_constant<int, 3>{}); break;
+        case 4: ok = hals(std::integral_constant<int, 4>{}); break;
+        case 5: ok = hals(std::integral_constant<int, 5>{}); break;
+        case 6: ok = hals(std::integral_constant<int, 6>{}); break;
+        case 7: ok = hals(std::integral_constant<int, 7>{}); break;
+        default: ok = hals(std::integral_constant<int, 8>{}); break;
+      }
+      if (!ok) return;
     }
-    if (!done) switch (N) {
-      case 1: ok = hals(std::integral_constant<int, 1>{}); break;
-      case 2: ok = hals(std::integral_constant<int, 2>{}); break;
-      case 3: ok = hals(std::integral_constant<int, 3>{}); break;
-      case 4: ok = hals(std::integral_constant<int, 4>{}); break;
-      case 5: ok = hals(std::integral_constant<int, 5>{}); break;
-      case 6: ok = hals(std::integral_constant<int, 6>{}); break;
-      case 7: ok = hals(std::integral_constant<int, 7>{}); break;
-      default: ok = hals(std::integral_constant<int, 8>{}); break;
-    }
-    if (!ok) return;
 
     // ------------------------------------------ scale to peak 1, export
     for (int n = 0; n < N; ++n) {
@@ -836,19 +840,24 @@ __global__ void k_fill_u32(unsigned* p, int n, unsigned v) {
   if (i < n) p[i] = v;
 }
 
-// Dynamic LDS of one workgroup: A [K][R8], F and P A^T [mw][R8], scratch
-// (F^T P totals, the chunk partials of the HALS products, the SPA vectors or
-// the final column maxima), P rows [mw][Kp].
+// Dynamic LDS of one workgroup: A [K][R8], F [mw][R8], F^T P totals [R8][K],
+// scratch (the chunk partials of the HALS products, the SPA vectors, the final
+// column maxima or the waves' sums of the sweeps in registers), P rows
+// [mw][Kp]. The HALS products need a double per row and rank at least: slices
+// of up to kSliceMax rows have that at every rank. (The sweeps in registers
+// need rows_scratch, whatever their rows.)
+constexpr int kSliceMax = 192, kScratch = kSliceMax * R8;
+static_assert(rows_scratch(kRowsK) <= kScratch, "the waves' sums fit the scratch");
 size_t split_lds(int K, int mw, int* scr_out) {
   const int Kp = K | 1;
-  const size_t scr = std::max<size_t>({(size_t)12 * 16 * R8, (size_t)K + mw});
+  const size_t scr = std::max<size_t>({(size_t)kScratch, (size_t)K + mw});
   if (scr_out) *scr_out = (int)scr;
   return 8 * ((size_t)K * R8 + (size_t)mw * R8 + (size_t)R8 * K + scr) + 4 * (size_t)mw * Kp;
 }
 
 }  // namespace
 
-bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff, size_t xbuf_bytes,
+bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff, const int* ranks, size_t xbuf_bytes,
                     NmfSplitTables& tab) {
   int dev = 0, coop = 0, ncu = 0, max_lds = 0, clock_khz = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
@@ -867,31 +876,24 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
   // exchange slots: two per workgroup of the largest launch, in xbuf, each
   // of XS high and XS low words
   const size_t slot_bytes = (size_t)2 * 2 * XS * 8;
+  // pixels of component k that this plan takes (none of one that is done)
+  auto pixels = [&](int k) { return ranks && ranks[k] != kNmfLeft ? 0 : coff[k + 1] - coff[k]; };
   // Slice widths in order of preference: 96 rows balance the per-sweep exchange
   // against the per-workgroup work where there are many segments, 160 where
   // there are few and a row is little work (at 60 segments 1.64 ms against
   // 1.86 for 96 rows and 1.81 for 208; at 90 2.34 against 2.39; at 120 1.79
-  // against 1.54). At most twelve 16-row tiles. Components are packed, in
-  // order, into launches of at most one workgroup per compute unit; each
-  // launch costs about the same (its sweeps are latency bound), so the width
-  // with the fewest launches wins.
+  // against 1.54). Components are packed, in order, into launches of at most
+  // one workgroup per compute unit; each launch costs about the same (its
+  // sweeps are latency bound), so the width with the fewest launches wins.
   const bool few = K <= 96;
-  // Short recordings whose components all fit one workgroup each take the
-  // sweeps in registers (0.25 ms against 0.86 at 8 segments, 0.32 against 0.90
-  // at 20, in registers first; 48 columns and the Gram entries are what the
-  // registers hold, and 512 rows of P_c and F what the LDS does).
-  int most = 0;
-  for (int k = 0; k < ncomp; ++k) most = std::max(most, coff[k + 1] - coff[k]);
-  const bool rows = K <= kRowsK && most <= kRowsMax;
-  const int widths[] = {rows ? (most + 63) / 64 * 64 : few ? 160 : 96, few ? 160 : 96, 128, few ? 96 : 160, 192, 64, 32};
-  int best_mw = 0, best_groups = 0;
-  for (const int mw : widths) {
-    int scr = 0;
-    if (split_lds(K, mw, &scr) > budget) continue;
+  const int widths[] = {few ? 160 : 96, 128, few ? 96 : 160, kSliceMax, 64, 32};
+  int mw = 0, best_groups = 0;
+  for (const int w : widths) {
+    if (split_lds(K, w, nullptr) > budget) continue;
     int groups = 1, in_group = 0, widest = 0;
     bool fits = true;
     for (int k = 0; k < ncomp && fits; ++k) {
-      const int nwk = (coff[k + 1] - coff[k] + mw - 1) / mw;
+      const int nwk = (pixels(k) + w - 1) / w;
       if (nwk > ncu) fits = false;
       else if (in_group + nwk > ncu) {
         ++groups;
@@ -902,22 +904,33 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
       widest = std::max(widest, in_group);
     }
     fits = fits && (size_t)widest * slot_bytes <= xbuf_bytes;
-    if (fits && (best_mw == 0 || groups < best_groups)) {
-      best_mw = mw;
+    if (fits && (mw == 0 || groups < best_groups)) {
+      mw = w;
       best_groups = groups;
     }
   }
-  if (best_mw == 0) return false;
-  const int mw = best_mw;
+  if (mw == 0) return false;
+  // Short recordings whose components all fit one workgroup each take the
+  // sweeps in registers (0.25 ms against 0.86 at 8 segments, 0.32 against 0.90
+  // at 20, in registers first; 48 columns and the Gram entries are what the
+  // registers hold, and 512 rows of P_c and F what the LDS does). Components
+  // that they leave have a plan of the other kind, since one was found above.
+  int most = 0;
+  for (int k = 0; k < ncomp; ++k) most = std::max(most, pixels(k));
+  const int one = (most + 63) / 64 * 64;
+  s.rows = !ranks && K <= kRowsK && most <= kRowsMax && split_lds(K, one, nullptr) <= budget;
+  if (s.rows) mw = one;
   int scr = 0;
   size_t lds = split_lds(K, mw, &scr);
-  // spare LDS (up to 3 R8 K more doubles) widens the scratch of the HALS
-  // products' chunk partials, so more chunks run at once at higher ranks
-  const size_t more = std::min<size_t>((budget - lds) / 8, (size_t)3 * R8 * K);
-  scr += (int)more;
-  lds += 8 * more;
+  if (!s.rows) {
+    if (scr < mw * R8) return false;   // a double per row and rank for the HALS products
+    // spare LDS (up to 3 R8 K more doubles) widens the scratch of the HALS
+    // products' chunk partials, so more chunks run at once at higher ranks
+    const size_t more = std::min<size_t>((budget - lds) / 8, (size_t)3 * R8 * K);
+    scr += (int)more;
+    lds += 8 * more;
+  }
   int occ = 0;
-  s.rows = rows && mw >= most;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, s.rows ? k_nmf_split<true> : k_nmf_split<false>,
                                                    s.rows ? 512 : 1024, lds) != hipSuccess || occ < 1)
     return false;
@@ -937,7 +950,7 @@ bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff,
   std::vector<std::vector<int>> members(1);
   int start = 0, in_group = 0;
   for (int k = 0; k < ncomp; ++k) {
-    const int nwk = (coff[k + 1] - coff[k] + mw - 1) / mw;
+    const int nwk = (pixels(k) + mw - 1) / mw;
     if (in_group + nwk > ncu) {
       tab.groups.push_back({start, in_group});
       members.emplace_back();

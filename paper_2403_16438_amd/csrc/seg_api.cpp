@@ -498,57 +498,12 @@ int seg_finalize(seg_session* s, void* stream) {
     // SPA-flag area (all three belong to the single-workgroup kernel)
     seg::NmfSplit sp{};
     seg::NmfSplitTables tabs;
-    bool split = c.nmf_path != SEG_NMF_SINGLE &&
-                 seg::plan_nmf_split(sp, na, coff, (size_t)s->M * s->Kmax * 8, tabs);
-    if (!split && c.nmf_path == SEG_NMF_SPLIT) return SEG_E_CAPACITY;
+    bool split = false;
     // cooperative grids of concurrent finalizes could each hold part of the
     // device while waiting for the rest: one split NMF at a time per process
     static std::mutex split_mutex;
     std::unique_lock<std::mutex> hold(split_mutex, std::defer_lock);
     std::vector<int> up;   // host tables of the split launch (kept until the stream is synchronised)
-    if (split) {
-      int* tab = at<int>(s, l.nmf_G);
-      const size_t G = tabs.comp.size();
-      // the four tables in one upload: comp [G], base [ncomp], n [ncomp], rank [G]
-      up.reserve(2 * G + 2 * (size_t)ncomp);
-      up.insert(up.end(), tabs.comp.begin(), tabs.comp.end());
-      up.insert(up.end(), tabs.base.begin(), tabs.base.end());
-      up.insert(up.end(), tabs.n.begin(), tabs.n.end());
-      up.insert(up.end(), tabs.rank.begin(), tabs.rank.end());
-      if ((e = fail(s, hipMemcpyAsync(tab, up.data(), up.size() * 4, hipMemcpyHostToDevice, st)))) return e;
-      int* rank = tab + G + 2 * (size_t)ncomp;
-      sp.wg_base = tab + G;
-      sp.wg_n = tab + G + ncomp;
-      sp.xbuf = reinterpret_cast<unsigned long long*>(na.P);
-      sp.sync = reinterpret_cast<unsigned*>(na.Wk);
-      hold.lock();
-      if ((e = fail(s, hipEventRecord(s->ev[2], st)))) return e;
-      // launches in order on the stream; each reuses the slots and counters
-      hipError_t le = hipSuccess;
-      for (size_t gi = 0; gi < tabs.groups.size(); ++gi) {
-        seg::NmfSplit one = sp;
-        one.G = tabs.groups[gi].second;
-        one.wg_comp = tab + tabs.groups[gi].first;
-        one.wg_rank = rank + tabs.groups[gi].first;
-        le = seg::launch_nmf_split(na, one, gi == 0, st);
-        if (le != hipSuccess) break;
-      }
-      if (le != hipSuccess) {
-        (void)hipGetLastError();
-        hold.unlock();
-        if (c.nmf_path == SEG_NMF_SPLIT || le != hipErrorCooperativeLaunchTooLarge) return fail(s, le);
-        split = false;  // the device is shared: one workgroup per component
-      }
-    }
-    if (!split) {
-      int max_mc = 0;
-      for (int k = 0; k < ncomp; ++k) max_mc = std::max(max_mc, coff[k + 1] - coff[k]);
-      seg::plan_nmf(na, max_mc);
-      if ((e = fail(s, hipEventRecord(s->ev[2], st)))) return e;
-      if ((e = fail(s, seg::launch_nmf(na, st)))) return e;
-    }
-    if ((e = fail(s, hipEventRecord(s->ev[3], st)))) return e;
-    nmf_timed = true;
     const size_t npx = pix.size(), nF = npx * seg::kMaxRank, nA = (size_t)ncomp * seg::kMaxRank * s->Kmax;
     unsigned split_error = 0;
     // The results (error flag, ranks, pixel lists, F, A) are packed into the
@@ -563,31 +518,88 @@ int seg_finalize(seg_session* s, void* stream) {
     const int* N = reinterpret_cast<const int*>(h + o_n);
     const double* F = reinterpret_cast<const double*>(h + o_f);
     const double* A = reinterpret_cast<const double*>(h + o_a);
-    const struct { const void* from; size_t at, bytes; } part[5] = {{na.N, o_n, (size_t)ncomp * 4},
-                                                                    {dpix, o_pix, npx * 4},
-                                                                    {na.F, o_f, nF * 8},
-                                                                    {na.A, o_a, nA * 8},
-                                                                    {split ? sp.sync + ncomp : nullptr, o_err, 4}};
-    const int parts = split ? 5 : 4;
-    hipError_t he = hipSuccess;
-    if (packed <= (size_t)s->M * s->Kmax * 8 && packed / 4 < 0xffffff00ULL) {
-      seg::PackArgs pk{};
-      pk.n = parts;
-      pk.dst = reinterpret_cast<uint32_t*>(na.P);
-      for (int k = 0; k < parts; ++k) {
-        pk.src[k] = static_cast<const uint32_t*>(part[k].from);
-        pk.words[k] = (uint32_t)(part[k].bytes / 4);
-        pk.at[k] = (uint32_t)(part[k].at / 4);
+    uint32_t workgroups = 0;
+    std::vector<int> left;
+    for (const int* ranks = nullptr;;) {
+      split = c.nmf_path != SEG_NMF_SINGLE &&
+              seg::plan_nmf_split(sp, na, coff, ranks, (size_t)s->M * s->Kmax * 8, tabs);
+      if (!split && c.nmf_path == SEG_NMF_SPLIT) return SEG_E_CAPACITY;
+      if (split) {
+        int* tab = at<int>(s, l.nmf_G);
+        const size_t G = tabs.comp.size();
+        up.clear();
+        // the four tables in one upload: comp [G], base [ncomp], n [ncomp], rank [G]
+        up.reserve(2 * G + 2 * (size_t)ncomp);
+        up.insert(up.end(), tabs.comp.begin(), tabs.comp.end());
+        up.insert(up.end(), tabs.base.begin(), tabs.base.end());
+        up.insert(up.end(), tabs.n.begin(), tabs.n.end());
+        up.insert(up.end(), tabs.rank.begin(), tabs.rank.end());
+        if ((e = fail(s, hipMemcpyAsync(tab, up.data(), up.size() * 4, hipMemcpyHostToDevice, st)))) return e;
+        int* rank = tab + G + 2 * (size_t)ncomp;
+        sp.wg_base = tab + G;
+        sp.wg_n = tab + G + ncomp;
+        sp.xbuf = reinterpret_cast<unsigned long long*>(na.P);
+        sp.sync = reinterpret_cast<unsigned*>(na.Wk);
+        if (!hold.owns_lock()) hold.lock();
+        if (!ranks && (e = fail(s, hipEventRecord(s->ev[2], st)))) return e;
+        // launches in order on the stream; each reuses the slots and counters
+        hipError_t le = hipSuccess;
+        for (size_t gi = 0; gi < tabs.groups.size(); ++gi) {
+          seg::NmfSplit one = sp;
+          one.G = tabs.groups[gi].second;
+          one.wg_comp = tab + tabs.groups[gi].first;
+          one.wg_rank = rank + tabs.groups[gi].first;
+          le = seg::launch_nmf_split(na, one, gi == 0, st);
+          if (le != hipSuccess) break;
+        }
+        if (le != hipSuccess) {
+          (void)hipGetLastError();
+          hold.unlock();
+          if (c.nmf_path == SEG_NMF_SPLIT || le != hipErrorCooperativeLaunchTooLarge) return fail(s, le);
+          split = false;  // the device is shared: one workgroup per component
+        }
       }
-      he = seg::launch_pack(pk, st);
-      if (he == hipSuccess) he = hipMemcpyAsync(h, na.P, packed, hipMemcpyDeviceToHost, st);
-    } else {
-      for (int k = 0; k < parts && he == hipSuccess; ++k)
-        he = hipMemcpyAsync(h + part[k].at, part[k].from, part[k].bytes, hipMemcpyDeviceToHost, st);
+      if (!split) {
+        int max_mc = 0;
+        for (int k = 0; k < ncomp; ++k) max_mc = std::max(max_mc, coff[k + 1] - coff[k]);
+        seg::plan_nmf(na, max_mc);
+        if (!ranks && (e = fail(s, hipEventRecord(s->ev[2], st)))) return e;
+        if ((e = fail(s, seg::launch_nmf(na, st)))) return e;
+      }
+      if ((e = fail(s, hipEventRecord(s->ev[3], st)))) return e;
+      nmf_timed = true;
+      const struct { const void* from; size_t at, bytes; } part[5] = {{na.N, o_n, (size_t)ncomp * 4},
+                                                                      {dpix, o_pix, npx * 4},
+                                                                      {na.F, o_f, nF * 8},
+                                                                      {na.A, o_a, nA * 8},
+                                                                      {split ? sp.sync + ncomp : nullptr, o_err, 4}};
+      const int parts = split ? 5 : 4;
+      hipError_t he = hipSuccess;
+      if (packed <= (size_t)s->M * s->Kmax * 8 && packed / 4 < 0xffffff00ULL) {
+        seg::PackArgs pk{};
+        pk.n = parts;
+        pk.dst = reinterpret_cast<uint32_t*>(na.P);
+        for (int k = 0; k < parts; ++k) {
+          pk.src[k] = static_cast<const uint32_t*>(part[k].from);
+          pk.words[k] = (uint32_t)(part[k].bytes / 4);
+          pk.at[k] = (uint32_t)(part[k].at / 4);
+        }
+        he = seg::launch_pack(pk, st);
+        if (he == hipSuccess) he = hipMemcpyAsync(h, na.P, packed, hipMemcpyDeviceToHost, st);
+      } else {
+        for (int k = 0; k < parts && he == hipSuccess; ++k)
+          he = hipMemcpyAsync(h + part[k].at, part[k].from, part[k].bytes, hipMemcpyDeviceToHost, st);
+      }
+      if (he == hipSuccess) he = hipStreamSynchronize(st);
+      if ((e = fail(s, he))) return e;
+      if (split) std::memcpy(&split_error, h + o_err, 4);
+      workgroups += split ? (uint32_t)sp.G : (uint32_t)ncomp;
+      // once more for the components that sweeps in registers have left
+      const int* end = N + ncomp;
+      if (!split || !sp.rows || std::find(N, end, seg::kNmfLeft) == end) break;
+      left.assign(N, end);
+      ranks = left.data();
     }
-    if (he == hipSuccess) he = hipStreamSynchronize(st);
-    if ((e = fail(s, he))) return e;
-    if (split) std::memcpy(&split_error, h + o_err, 4);
     std::memcpy(pix.data(), h + o_pix, npx * 4);
     if (hold.owns_lock()) hold.unlock();
     if (split_error) return fail(s, hipErrorLaunchTimeOut);  // a wait for a slot was abandoned
@@ -607,7 +619,7 @@ int seg_finalize(seg_session* s, void* stream) {
       s->prof.nmf_flops = fl;
       s->prof.max_rank = rmax;
       s->prof.nmf_path = split ? SEG_NMF_SPLIT : SEG_NMF_SINGLE;
-      s->prof.nmf_workgroups = split ? (uint32_t)sp.G : (uint32_t)ncomp;
+      s->prof.nmf_workgroups = workgroups;
     }
     const double level = (double)c.footprint_level;
     for (int k = 0; k < ncomp; ++k) {

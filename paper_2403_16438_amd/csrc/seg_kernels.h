@@ -123,8 +123,12 @@ struct NmfSplitTables {
 };
 // Chooses the slice width (fewest launches of at most one workgroup per
 // compute unit that fit LDS and xbuf_bytes) and packs the components into
-// launches; false when the split path does not apply.
-bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff, size_t xbuf_bytes,
+// launches; false when the split path does not apply. A plan with `rows` set
+// may leave components of higher rank: their N is kNmfLeft afterwards. With
+// the ranks of such a run given, the plan takes the components that were left,
+// and leaves none.
+constexpr int kNmfLeft = -1;
+bool plan_nmf_split(NmfSplit& s, const NmfArgs& a, const std::vector<int>& coff, const int* ranks, size_t xbuf_bytes,
                     NmfSplitTables& tab);
 // One launch of the plan (s.G and s.wg_comp select it): clears its exchange
 // slots first; `first` also clears the abandon and error flags.

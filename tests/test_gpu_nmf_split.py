@@ -16,6 +16,7 @@ from paper_2403_16438_amd import Session, abi, segment_video
 from synth import preset, simulate
 
 from parity import compare_footprints, params_from_config
+from scenes import ring_video
 
 pytestmark = pytest.mark.gpu
 
@@ -205,3 +206,58 @@ def test_sweeps_in_registers(K):
     assert np.array_equal(one["masks"], two["masks"])
     assert np.abs(one["weights"] - two["weights"]).max() <= 1e-5
     assert np.abs(one["activity"] - two["activity"]).max() <= 1e-5 * np.abs(one["activity"]).max()
+
+
+def _cluster(T, cy, cx, n, q, r, rng):
+    """n cells of radius r on a ring of radius q, one at a time active: one
+    component of rank n."""
+    yy, xx = np.mgrid[0:T.shape[1], 0:T.shape[2]]
+    for i in range(len(T)):
+        a = 2 * np.pi * (i % n) / n
+        d2 = (yy - cy - q * np.sin(a)) ** 2 + (xx - cx - q * np.cos(a)) ** 2
+        T[i] += np.where(d2 <= r * r, rng.uniform(8, 14) * (1.3 - d2 / (r * r + 1.0)), 0.0).astype(np.float32)
+
+
+@pytest.mark.parametrize("K", [8, 20, 44])
+@pytest.mark.parametrize("n,q,r", [(4, 7.5, 6.5), (5, 7.5, 6), (6, 7.5, 6), (7, 8, 5.5), (8, 8.5, 5)])
+def test_higher_ranks_in_short_recordings(n, q, r, K):
+    """Components of at most 512 pixels over at most 44 segments whose rank is
+    more than the sweeps in registers take, beside some of rank 1 to 3 (of more
+    and of less than 256 pixels) that they do take: both paths, which differ in
+    the order of FP64 sums only, to the bars of the comparison above."""
+    rng = np.random.default_rng(100 * n + K)
+    T = rng.uniform(0.5, 1.5, (K, 64, 192)).astype(np.float32)
+    _cluster(T, 32, 32, n, q, r, rng)
+    _cluster(T, 32, 96, 3, 6, 6.5, rng)
+    _cluster(T, 16, 150, 2, 3, 4, rng)
+    _cluster(T, 48, 150, 1, 0, 4, rng)
+    D = np.full(T.shape, 1.0 / np.sqrt(2 * np.pi), np.float32)
+    got = []
+    for path in (abi.SEG_NMF_SINGLE, abi.SEG_NMF_SPLIT):
+        s = Session(64, 192, 50 * K, nmf_path=path, min_event_segs=1, nmf_max_rank=8)
+        s.load_summaries(T, np.ones_like(T), D)
+        s.finalize()
+        torch.cuda.synchronize()
+        prof = s.profile()
+        assert prof["nmf_path"] == path and prof["max_rank"] == n
+        sizes = np.sort(np.bincount(s.image(abi.SEG_IMG_LABELS).ravel())[1:])
+        assert len(sizes) == 4 and 450 <= sizes[-1] <= 512 and 256 < sizes[-2] <= 512
+        got.append(s.footprints())
+        s.close()
+    one, two = got
+    assert len(one["component"]) == n + 6
+    assert np.array_equal(one["component"], two["component"])
+    assert np.array_equal(one["masks"], two["masks"])
+    assert np.abs(one["weights"] - two["weights"]).max() <= 1e-5
+    assert np.abs(one["activity"] - two["activity"]).max() <= 1e-5 * np.abs(one["activity"]).max()
+
+
+@pytest.mark.parametrize("n,radius,sigma,frames", [(6, 5.0, 2.0, 1000), (5, 5.0, 2.0, 500), (4, 5.0, 2.5, 500)])
+def test_short_recordings_of_a_ring(n, radius, sigma, frames):
+    """The same from frames, with the default limits: against the oracle."""
+    video = ring_video(n_cells=n, radius=radius, sigma=sigma, frames=frames)
+    sess = segment_video(video)
+    ref = oracle.segment(video, params_from_config(sess.cfg))
+    prof = sess.profile()
+    assert prof["nmf_path"] == abi.SEG_NMF_SPLIT and prof["max_rank"] >= 4
+    compare_footprints(sess.footprints(), ref.footprints)
