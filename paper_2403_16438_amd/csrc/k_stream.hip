@@ -48,7 +48,8 @@
 // 64 x 64 x 50 99 -> 81 us, 450 x 138 x 500 561 -> 171 us, four recordings of
 // 500 frames in one launch (128 x 128 to 512 x 512) 1,520 -> 1,005 us (the four
 // bytes above: 80, 168 and 1,000 us). 256 x 256 x 1,600: 578 -> 455 us, the same
-// with bright frames in every segment, and 582 -> 625 us with values over the whole 16-bit range,
+// with bright frames in every segment, and 582 -> 587 us with values over the whole 16-bit range
+// (138 x 450 x 500 487 -> 212 us),
 // which takes the general path.
 //
 // Every thread owns 4 adjacent pixels of one tile row and keeps their 50
@@ -323,17 +324,12 @@ __device__ __forceinline__ bool store_pixels(const Out& p, int sl, int gy, int g
   return faint;
 }
 
-// The general path: FP64 sums of d in FP32, from the segment's first frame. A
-// function of its own, with its own registers. NARROW: rows of fewer than four
-// pixels.
+// The general path: FP64 sums of d in FP32, from the segment's first frame, so
+// that no register lives on from the fixed-point path: with its window and
+// scale handed over in one body, frames that all come here took 660 us at
+// 256 x 256 x 1,600 (now 587). NARROW: rows of fewer than four pixels.
 template <bool NARROW>
-__device__ __attribute__((noinline)) void general_segment(ConstParams params, int sl_, int tile_, LdsSmem lds) {
-  // arguments come in vector registers
-  const uint64_t pa = (uint64_t)params;
-  const ConstParams p = (ConstParams)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(pa >> 32)) << 32 |
-                                      (uint32_t)__builtin_amdgcn_readfirstlane((int)pa));
-  Smem& sm = *(Smem*)(LdsSmem)(uintptr_t)((uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)lds) & ~15u);   // aligned, to the compiler
-  const int sl = __builtin_amdgcn_readfirstlane(sl_), tile = __builtin_amdgcn_readfirstlane(tile_);
+__device__ __forceinline__ void general_segment(ConstParams p, int sl, int tile, Smem& sm) {
   const Out out = outputs(p);
   const int H = out.H, W = out.W;
   double w[NTAP];
@@ -739,10 +735,27 @@ __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int ti
   return !__builtin_amdgcn_readfirstlane(sm.leave[NCH]);
 }
 
+// The general path called: its arguments come in vector registers, and the
+// compiler is to know that the LDS is aligned (four-byte LDS reads otherwise:
+// 625 -> 655 us). The batch kernel, short of registers for its loop over items,
+// and narrow frames call it; a call saves 112 registers per thread, and where
+// all segments take it costs 610 us instead of 587.
+template <bool NARROW>
+__device__ __attribute__((noinline)) void general_call(ConstParams params, int sl, int tile, LdsSmem lds) {
+  const uint64_t p = (uint64_t)params;
+  const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)lds) & ~15u;
+  general_segment<NARROW>((ConstParams)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32 |
+                                        (uint32_t)__builtin_amdgcn_readfirstlane((int)p)),
+                          __builtin_amdgcn_readfirstlane(sl), __builtin_amdgcn_readfirstlane(tile),
+                          *(Smem*)(LdsSmem)(uintptr_t)at);
+}
+
+template <bool CALL>
 __device__ __forceinline__ void work_item(ConstParams params, int sl, int tile, Smem& sm) {
   if (fixed_segment(params, sl, tile, sm)) return;
-  if (params->W < 4) general_segment<true>(params, sl, tile, (LdsSmem)&sm);
-  else general_segment<false>(params, sl, tile, (LdsSmem)&sm);
+  if (params->W < 4) general_call<true>(params, sl, tile, (LdsSmem)&sm);
+  else if (CALL) general_call<false>(params, sl, tile, (LdsSmem)&sm);
+  else general_segment<false>(params, sl, tile, sm);
 }
 
 __global__ __launch_bounds__(NT, 2) void k_block_stats(KParams p) {
@@ -758,7 +771,7 @@ __global__ __launch_bounds__(NT, 2) void k_block_stats(KParams p) {
   const int logical = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (logical >= nblk) return;
   const int sl = logical / ntile;
-  work_item((ConstParams)__builtin_amdgcn_kernarg_segment_ptr(), sl, logical - sl * ntile, sm);
+  work_item<false>((ConstParams)__builtin_amdgcn_kernarg_segment_ptr(), sl, logical - sl * ntile, sm);
 }
 
 // Serving: one persistent launch over the work items of several recordings
@@ -775,7 +788,7 @@ __global__ __launch_bounds__(NT, 2) void k_block_stats_batch(const BatchTable* _
     const int local = item - bs.item0;
     const int sl = local / bs.ntile;
     const int tile = local - sl * bs.ntile;
-    work_item((ConstParams)&bs.p, sl, tile, sm);
+    work_item<true>((ConstParams)&bs.p, sl, tile, sm);
     __syncthreads();
   }
 }
