@@ -84,7 +84,9 @@ struct Plan {
   Buf wr;              // 3 x 3 convolution weights reordered for the direct kernel
   size_t wr_off[NPAR]; // element offset of each 3 x 3 layer in wr
   Buf wd;              // and for its input gradient, the same offsets
-  Buf part, bpart;     // partial sums of the weight and bias gradients
+  // partial sums of the weight and bias gradients: over col, dcol and splitk,
+  // which the layers without a direct kernel use (see Grads)
+  Buf part, bpart;
   size_t total;
 };
 
@@ -145,6 +147,13 @@ Plan make_plan(int B, int H, int W, bool st) {
   p.gd1a = take(f * 32 * N);
   p.gd1 = take(f * 32 * N);
   p.glogit = take(f * N);
+  const PDef* P = st ? kPst : kP;
+  size_t reordered = 0;   // elements of the 3 x 3 layers' reordered weights
+  for (int i = 0; i < NPAR; ++i) {
+    p.wr_off[i] = reordered;
+    if (P[i].rows > 0 && P[i].cols % 9 == 0 && i >= E1A && i != U2 && i != U1 && i != FO)
+      reordered += (conv3_reordered_size(P[i].rows, P[i].cols / 9) + 7) / 8 * 8;
+  }
   // largest im2col: 160 rows x 5N (t2) vs 576 rows x N (d1a) vs 1152 x N2 ...
   long long colmax = 160 * 5 * N;
   colmax = std::max(colmax, 5LL * 10 * N);
@@ -153,31 +162,29 @@ Plan make_plan(int B, int H, int W, bool st) {
   colmax = std::max(colmax, 1152LL * N4);
   p.col = take(2 * colmax);
   p.dcol = take(f * colmax);
-  p.splitk = take(f * (size_t)SPLITS * 256 * 1152);
+  // the split weight gradients of the largest layer need half of this; what the
+  // input gradients' weight copies take comes off it
+  const size_t split = f * (size_t)SPLITS * 256 * 1152, copies = (2 * reordered + 255) & ~size_t(255);
+  p.splitk = take(split - copies);
+  {
+    // pixels that each layer's weight gradient sums over
+    const long long full[NPAR] = {10 * N, 5 * N, N, N, N, N2, N2, N4, N4, N4, N2, N2, N2, N, N, N};
+    size_t sums = 0, channels = 0;
+    for (int i = 0; i < NPAR; ++i) {
+      const long long z = std::min<long long>(kGradSplits, (full[i] + 31) / 32);
+      sums += ((size_t)z * P[i].rows * P[i].cols + 3) / 4 * 4;
+      channels += bias_len(P, i);
+    }
+    p.bpart = Buf{p.col.off, f * 256 * channels};
+    p.part = Buf{p.col.off + p.bpart.bytes, f * sums};
+    const size_t end = p.part.off + p.part.bytes;
+    if (end > at) take(end - at);   // (not so at any size: the shared space is at least 1.4 times this)
+  }
   p.lossp = take(f * ((N + 255) / 256 + 1));
   const POff po = param_offsets(st ? kPst : kP);
   p.wb = take(2 * po.total);
-  {
-    const PDef* P = st ? kPst : kP;
-    size_t at_wr = 0;
-    for (int i = 0; i < NPAR; ++i) {
-      p.wr_off[i] = at_wr;
-      if (P[i].rows > 0 && P[i].cols % 9 == 0 && i >= E1A && i != U2 && i != U1 && i != FO)
-        at_wr += (conv3_reordered_size(P[i].rows, P[i].cols / 9) + 7) / 8 * 8;
-    }
-    p.wr = take(2 * at_wr);
-    p.wd = take(2 * at_wr);
-    // pixels that each layer's weight gradient sums over
-    const long long full[NPAR] = {10 * N, 5 * N, N, N, N, N2, N2, N4, N4, N4, N2, N2, N2, N, N, N};
-    size_t at_part = 0, channels = 0;
-    for (int i = 0; i < NPAR; ++i) {
-      const long long z = std::min<long long>(kGradSplits, (full[i] + 31) / 32);
-      at_part += ((size_t)z * P[i].rows * P[i].cols + 3) / 4 * 4;
-      channels += bias_len(P, i);
-    }
-    p.part = take(f * at_part);
-    p.bpart = take(f * 256 * channels);
-  }
+  p.wr = take(2 * reordered);
+  p.wd = take(2 * reordered);
   p.grad = take(f * po.total);
   p.vel = take(f * po.total);
   p.total = at;
@@ -293,15 +300,29 @@ hipError_t conv3(seg_nn* n, int id, const float* X, int Bn, int H, int W, float*
 }
 
 // The gradients of a backward pass: the layers whose sums over pixels are
-// added at its end by grad_reduce, and what is left of the partial sums' space.
+// added by grad_reduce, at its end or before a layer without a direct kernel
+// takes the partial sums' space for its im2col matrix or split products, and
+// what is left of that space.
 struct Grads {
-  GradTable t{};
+  seg_nn* n;
+  GradTable t;
   float* part;
   float* bpart;
-  int channels = 0;
-  Grads(seg_nn* n) : part(at<float>(n, n->plan.part)), bpart(at<float>(n, n->plan.bpart)) { t.bpart = bpart; }
+  int channels;
+  Grads(seg_nn* net) : n(net) { clear(); }
+  void clear() {
+    t = GradTable{};
+    part = at<float>(n, n->plan.part);
+    bpart = at<float>(n, n->plan.bpart);
+    t.bpart = bpart;
+    channels = 0;
+  }
+  void reduce(hipStream_t st) {
+    if (t.nw || t.nb) grad_reduce(t, at<float>(n, n->plan.grad), st);
+    clear();
+  }
   // a bias gradient of C channels: where its chains go
-  float* bias(seg_nn* n, int id) {
+  float* bias(int id) {
     float* p = bpart + (size_t)channels * 256;
     const int C = bias_len(n->P, id);
     t.b[t.nb++] = BiasSeg{(long long)n->po.b[id], C, channels};
@@ -309,7 +330,7 @@ struct Grads {
     return p;
   }
   // a weight gradient [M][C T] whose partial sums were launched at `part`
-  void weight(seg_nn* n, int id, int T, long long K) {
+  void weight(int id, int T, long long K) {
     const int M = n->P[id].rows, C = n->P[id].cols / T, Z = grad_ranges(K);
     t.w[t.nw++] = GradSeg{part, (long long)n->po.w[id], M, C, T, Z, t.wblocks};
     t.wblocks += (M * C * T + 255) / 256;
@@ -320,9 +341,10 @@ struct Grads {
 // weight gradient dW = dY X^T of a layer whose product rows are rows of X
 hipError_t lin_dw(seg_nn* n, Grads& g, int id, const float* dY, const float* X, long long K, hipStream_t st) {
   if (dw1(dY, X, g.part, n->P[id].rows, n->P[id].cols, K, 1, 1, 0, 0, K, st)) {
-    g.weight(n, id, 1, K);
+    g.weight(id, 1, K);
     return hipSuccess;
   }
+  g.reduce(st);
   return gemm_dw(n, id, dY, X, false, K, st);
 }
 
@@ -330,9 +352,10 @@ hipError_t lin_dw(seg_nn* n, Grads& g, int id, const float* dY, const float* X, 
 hipError_t temporal_dw(seg_nn* n, Grads& g, int id, const float* dY, const float* X, int C, int Tin, int Tout, int S,
                        int Pd, long long N, hipStream_t st) {
   if (dw1(dY, X, g.part, n->P[id].rows, n->P[id].cols, Tout * N, Tin, 5, S, Pd, N, st)) {
-    g.weight(n, id, 1, Tout * N);
+    g.weight(id, 1, Tout * N);
     return hipSuccess;
   }
+  g.reduce(st);
   uint16_t* col = at<uint16_t>(n, n->plan.col);
   im2col1(X, col, C, Tin, Tout, 5, S, Pd, N, st);
   return gemm_dw(n, id, dY, col, true, Tout * N, st);
@@ -346,13 +369,15 @@ hipError_t conv3_bwd(seg_nn* n, Grads& g, int id, const float* X, const float* d
   const long long N = (long long)Bn * H * W;
   hipError_t e = hipSuccess;
   if (dw3(dY, X, g.part, Co, Ci, Bn, H, W, st)) {
-    g.weight(n, id, 9, N);
+    g.weight(id, 9, N);
   } else {
+    g.reduce(st);
     uint16_t* col = at<uint16_t>(n, n->plan.col);
     im2col3(X, col, Ci, Bn, H, W, st);
     if ((e = gemm_dw(n, id, dY, col, true, N, st)) != hipSuccess) return e;
   }
   if (!dX || dx3(at<uint16_t>(n, n->plan.wd) + n->plan.wr_off[id], dY, dX, Co, Ci, Bn, H, W, st, &e)) return e;
+  g.reduce(st);
   float* dcol = at<float>(n, n->plan.dcol);
   e = gemm_wtdy(n, id, dY, N, dcol, st);
   col2im3(dcol, dX, Ci, Bn, H, W, false, st);
@@ -536,22 +561,22 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* d1 = at<float>(n, p.d1);
   float* gd1 = at<float>(n, p.gd1);
   // output 1x1, and what it passes down
-  bias_mask(gl, nullptr, g.bias(n, FO), 1, N, st);
+  bias_mask(gl, nullptr, g.bias(FO), 1, N, st);
   chk(lin_dw(n, g, FO, gl, d1, N, st));
-  bias_outer(gl, wbf(n, FO), gd1, d1, g.bias(n, D1B), n->P[FO].cols, N, st);
+  bias_outer(gl, wbf(n, FO), gd1, d1, g.bias(D1B), n->P[FO].cols, N, st);
   // d1b, d1a
   float* d1a = at<float>(n, p.d1a);
   float* gd1a = at<float>(n, p.gd1a);
   float* cat1 = at<float>(n, p.cat1);
   float* gcat1 = at<float>(n, p.gcat1);
   chk(conv3_bwd(n, g, D1B, d1a, gd1, Bn, H, W, gd1a, st));
-  bias_mask(gd1a, d1a, g.bias(n, D1A), n->P[D1A].rows, N, st);
+  bias_mask(gd1a, d1a, g.bias(D1A), n->P[D1A].rows, N, st);
   chk(conv3_bwd(n, g, D1A, cat1, gd1a, Bn, H, W, gcat1, st));
   // u1: channels 0..31 of cat1 came from the transposed convolution
   float* gz1 = at<float>(n, p.gz1);
   float* d2 = at<float>(n, p.d2);
   float* gd2 = at<float>(n, p.gd2);
-  bias_mask(gcat1, nullptr, g.bias(n, U1), 32, N, st);
+  bias_mask(gcat1, nullptr, g.bias(U1), 32, N, st);
   up_gather(gcat1, gz1, 32, Bn, H / 2, W / 2, st);
   chk(lin_dw(n, g, U1, gz1, d2, N2, st));
   lin_dx(wbf(n, U1), gz1, gd2, n->P[U1].cols, n->P[U1].rows, N2, st);
@@ -560,15 +585,15 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* gd2a = at<float>(n, p.gd2a);
   float* cat2 = at<float>(n, p.cat2);
   float* gcat2 = at<float>(n, p.gcat2);
-  bias_mask(gd2, d2, g.bias(n, D2B), n->P[D2B].rows, N2, st);
+  bias_mask(gd2, d2, g.bias(D2B), n->P[D2B].rows, N2, st);
   chk(conv3_bwd(n, g, D2B, d2a, gd2, Bn, H / 2, W / 2, gd2a, st));
-  bias_mask(gd2a, d2a, g.bias(n, D2A), n->P[D2A].rows, N2, st);
+  bias_mask(gd2a, d2a, g.bias(D2A), n->P[D2A].rows, N2, st);
   chk(conv3_bwd(n, g, D2A, cat2, gd2a, Bn, H / 2, W / 2, gcat2, st));
   // u2: channels 0..63 of cat2
   float* gz2 = at<float>(n, p.gz2);
   float* b3 = at<float>(n, p.b3);
   float* gb3 = at<float>(n, p.gb3);
-  bias_mask(gcat2, nullptr, g.bias(n, U2), 64, N2, st);
+  bias_mask(gcat2, nullptr, g.bias(U2), 64, N2, st);
   up_gather(gcat2, gz2, 64, Bn, H / 4, W / 4, st);
   chk(lin_dw(n, g, U2, gz2, b3, N4, st));
   lin_dx(wbf(n, U2), gz2, gb3, n->P[U2].cols, n->P[U2].rows, N4, st);
@@ -577,9 +602,9 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* ge3a = at<float>(n, p.ge3a);
   float* p2 = at<float>(n, p.p2);
   float* gp2 = at<float>(n, p.gp2);
-  bias_mask(gb3, b3, g.bias(n, E3B), n->P[E3B].rows, N4, st);
+  bias_mask(gb3, b3, g.bias(E3B), n->P[E3B].rows, N4, st);
   chk(conv3_bwd(n, g, E3B, e3a, gb3, Bn, H / 4, W / 4, ge3a, st));
-  bias_mask(ge3a, e3a, g.bias(n, E3A), n->P[E3A].rows, N4, st);
+  bias_mask(ge3a, e3a, g.bias(E3A), n->P[E3A].rows, N4, st);
   chk(conv3_bwd(n, g, E3A, p2, ge3a, Bn, H / 4, W / 4, gp2, st));
   // skip 2 = channels 64..127 of cat2: its gradient is the concat part plus the pool path
   float* gs2 = gcat2 + 64 * N2;
@@ -588,9 +613,9 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* ge2a = at<float>(n, p.ge2a);
   float* p1 = at<float>(n, p.p1);
   float* gp1 = at<float>(n, p.gp1);
-  bias_mask(gs2, cat2 + 64 * N2, g.bias(n, E2B), n->P[E2B].rows, N2, st);
+  bias_mask(gs2, cat2 + 64 * N2, g.bias(E2B), n->P[E2B].rows, N2, st);
   chk(conv3_bwd(n, g, E2B, e2a, gs2, Bn, H / 2, W / 2, ge2a, st));
-  bias_mask(ge2a, e2a, g.bias(n, E2A), n->P[E2A].rows, N2, st);
+  bias_mask(ge2a, e2a, g.bias(E2A), n->P[E2A].rows, N2, st);
   chk(conv3_bwd(n, g, E2A, p1, ge2a, Bn, H / 2, W / 2, gp1, st));
   float* gs1 = gcat1 + 32 * N;
   pool_bwd(gp1, at<uint8_t>(n, p.arg1), gs1, 32 * Bn, H, W, true, st);
@@ -598,39 +623,40 @@ hipError_t backward(seg_nn* n, int Bn, hipStream_t st) {
   float* ge1a = at<float>(n, p.ge1a);
   float* a3 = at<float>(n, p.a3);
   float* ga3 = at<float>(n, p.ga3);
-  bias_mask(gs1, cat1 + 32 * N, g.bias(n, E1B), n->P[E1B].rows, N, st);
+  bias_mask(gs1, cat1 + 32 * N, g.bias(E1B), n->P[E1B].rows, N, st);
   chk(conv3_bwd(n, g, E1B, e1a, gs1, Bn, H, W, ge1a, st));
   if (n->st) {   // the input needs no gradient
-    bias_mask(ge1a, e1a, g.bias(n, E1A), n->P[E1A].rows, N, st);
+    bias_mask(ge1a, e1a, g.bias(E1A), n->P[E1A].rows, N, st);
     chk(conv3_bwd(n, g, E1A, at<float>(n, p.x0), ge1a, Bn, H, W, nullptr, st));
-    grad_reduce(g.t, at<float>(n, p.grad), st);
+    g.reduce(st);
     chk(hipGetLastError());
     return e;
   }
-  bias_mask(ge1a, e1a, g.bias(n, E1A), n->P[E1A].rows, N, st);
+  bias_mask(ge1a, e1a, g.bias(E1A), n->P[E1A].rows, N, st);
   chk(conv3_bwd(n, g, E1A, a3, ge1a, Bn, H, W, ga3, st));
   // temporal convolutions
   float* a2 = at<float>(n, p.a2);
   float* ga2 = at<float>(n, p.ga2);
-  bias_mask(ga3, a3, g.bias(n, T3), 32, N, st);
+  bias_mask(ga3, a3, g.bias(T3), 32, N, st);
   chk(lin_dw(n, g, T3, ga3, a2, N, st));
   float* a1 = at<float>(n, p.a1);
   float* ga1 = at<float>(n, p.ga1);
   if (temporal_dx(wbf(n, T2), wbf(n, T3), ga3, a2, a1, ga2, ga1, N, st)) {   // masked
-    bias_mask(ga2, nullptr, g.bias(n, T2), 32, 5 * N, st);
+    bias_mask(ga2, nullptr, g.bias(T2), 32, 5 * N, st);
     chk(temporal_dw(n, g, T2, ga2, a1, 32, 10, 5, 2, 2, N, st));
-    bias_mask(ga1, nullptr, g.bias(n, T1), 32, 10 * N, st);
+    bias_mask(ga1, nullptr, g.bias(T1), 32, 10 * N, st);
   } else {
     chk(gemm_wtdy(n, T3, ga3, N, ga2, st));
     float* dcol = at<float>(n, p.dcol);
-    bias_mask(ga2, a2, g.bias(n, T2), 32, 5 * N, st);
+    bias_mask(ga2, a2, g.bias(T2), 32, 5 * N, st);
     chk(temporal_dw(n, g, T2, ga2, a1, 32, 10, 5, 2, 2, N, st));
+    g.reduce(st);
     chk(gemm_wtdy(n, T2, ga2, 5 * N, dcol, st));
     col2im1(dcol, ga1, 32, 10, 5, 5, 2, 2, N, st);
-    bias_mask(ga1, a1, g.bias(n, T1), 32, 10 * N, st);
+    bias_mask(ga1, a1, g.bias(T1), 32, 10 * N, st);
   }
   chk(temporal_dw(n, g, T1, ga1, at<float>(n, p.x0), 1, L, 10, 5, 0, N, st));
-  grad_reduce(g.t, at<float>(n, p.grad), st);
+  g.reduce(st);
   chk(hipGetLastError());
   return e;
 }
