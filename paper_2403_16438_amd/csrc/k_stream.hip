@@ -56,7 +56,6 @@
 // smoothed values in VGPRs (40) and a per-thread LDS slot (the chunk being
 // filled); after the segment a compare-exchange network gives the median, the
 // maximum and the 25 smallest values.
-#include <algorithm>
 #include <cmath>
 
 #include "seg_kernels.h"
@@ -82,12 +81,11 @@ struct KParams {
   const uint16_t* src1;
   long long n0;
   int H, W;
-  int seg0, nseg;
+  int seg0;
+  float quiet;   // T from which the fixed point is as exact as FP32 at scale 0
   float *T, *S, *D, *U, *P;
   long long plane;
   double w[NTAP];
-  int wbits;     // the weights are whole numbers of 2^-wbits
-  float quiet;   // T from which the fixed point is as exact as FP32 at scale 0
 };
 
 struct BatchSlot {
@@ -481,7 +479,10 @@ __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int ti
 
   // ---- per-pixel reference: median of the segment's first three frames, and
   // the tile's scale from the largest |V - R| among them
-  const int wbits = params->wbits;
+  // the weights as whole numbers of 2^-wbits: the largest and its byte carries
+  // are below 2^31
+  const double most = params->w[RAD];
+  const int wbits = __builtin_amdgcn_readfirstlane(most > 0.99 ? 30 : most > 0.49 ? 31 : 32);
   uint32_t R[4][2];
   int e;
   {
@@ -729,7 +730,8 @@ __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int ti
   lds_barrier();
   const uint2 rr = *reinterpret_cast<const uint2*>(&sm.r16[hy * (TW / 2) + hx0 / 2]);
   const float rref[NPX] = {(float)(rr.x & 0xffffu), (float)(rr.x >> 16), (float)(rr.y & 0xffffu), (float)(rr.y >> 16)};
-  if (store_pixels(out, sl, ty0 + hy, tx0 + hx0, win, Wl + tid, Uacc, Pacc, rref, params->quiet * __builtin_ldexpf(1.f, -least)))
+  const float quiet = params->quiet * __builtin_ldexpf(1.f, -least);
+  if (store_pixels(out, sl, ty0 + hy, tx0 + hx0, win, Wl + tid, Uacc, Pacc, rref, quiet))
     sm.leave[NCH] = 1;
   __syncthreads();
   return !__builtin_amdgcn_readfirstlane(sm.leave[NCH]);
@@ -758,12 +760,12 @@ __device__ __forceinline__ void work_item(ConstParams params, int sl, int tile, 
   else general_segment<false>(params, sl, tile, sm);
 }
 
-__global__ __launch_bounds__(NT, 2) void k_block_stats(KParams p) {
+__global__ __launch_bounds__(NT, 2) void k_block_stats(KParams p, int nseg) {
   __shared__ Smem sm;
   const int tiles_x = (p.W + TW - 1) / TW;
   const int tiles_y = (p.H + TH - 1) / TH;
   const int ntile = tiles_x * tiles_y;
-  const int nblk = ntile * p.nseg;
+  const int nblk = ntile * nseg;
   // Blocks are dealt round-robin over the 8 XCDs; give every XCD a
   // contiguous range of (segment, tile) pairs so that neighbouring tiles of a
   // segment share their halo rows in one L2.
@@ -804,21 +806,17 @@ KParams params_of(const StreamLaunch& a) {
   p.H = a.H;
   p.W = a.W;
   p.seg0 = a.seg0;
-  p.nseg = a.nseg;
   p.T = a.T;
   p.S = a.S;
   p.D = a.D;
   p.U = a.U;
   p.P = a.P;
   p.plane = a.plane;
-  double top = 0.0, gain = 0.0;
+  double gain = 0.0;
   for (int k = 0; k < NTAP; ++k) {
     p.w[k] = a.w[k];
-    top = std::max(top, a.w[k]);
     gain += a.w[k] * a.w[k];
   }
-  // the largest weight and its byte carries below 2^31
-  p.wbits = top > 0.99 ? 30 : top > 0.49 ? 31 : 32;
   p.quiet = (float)(0.1 * std::sqrt(gain));
   return p;
 }
@@ -829,7 +827,7 @@ hipError_t launch_block_stats(const StreamLaunch& a, hipStream_t st) {
   const int tiles = ((a.W + TW - 1) / TW) * ((a.H + TH - 1) / TH);
   const long long nblk = (long long)tiles * a.nseg;
   const long long per = (nblk + 7) / 8;
-  hipLaunchKernelGGL(k_block_stats, dim3((unsigned)(per * 8)), dim3(NT), 0, st, p);
+  hipLaunchKernelGGL(k_block_stats, dim3((unsigned)(per * 8)), dim3(NT), 0, st, p, a.nseg);
   return hipGetLastError();
 }
 
