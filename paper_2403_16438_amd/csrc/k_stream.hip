@@ -286,7 +286,7 @@ __device__ __forceinline__ void keep(const float4* Wl, float (&w)[CH][NPX]) {
 // a pixel whose own value varies has a T below `quiet`.
 __device__ __forceinline__ bool store_pixels(const Out& p, int sl, int gy, int gx0, const float (&win)[NCH - 1][CH][NPX],
                                              const float4* Wl, const float (&Uacc)[NPX], const float (&Pacc)[5][NPX],
-                                             const float (&rref)[NPX], float quiet) {
+                                             const float (&rref)[NPX], double unit, float quiet) {
   bool faint = false;
 #pragma unroll
   for (int i = 0; i < NPX; ++i) {
@@ -309,10 +309,10 @@ __device__ __forceinline__ bool store_pixels(const Out& p, int sl, int gy, int g
     const int gx = gx0 + i;
     if (gy < p.H && gx < p.W) {
       const long long o = (long long)(p.seg0 + sl) * p.H * p.W + (long long)gy * p.W + gx;
-      const float T = (float)((double)v[SELNET50_MAX] - med);
+      const float T = (float)(((double)v[SELNET50_MAX] - med) * unit);
       faint |= Pacc[0][i] > 0.f && T < quiet;
       p.T[o] = T;
-      p.D[o] = (float)(dsum / (double)L);
+      p.D[o] = (float)(dsum * unit / (double)L);
       p.S[o] = (float)(((double)L * (double)rref[i] + (double)Uacc[i]) / (double)L);
       p.U[o] = Uacc[i];
 #pragma unroll
@@ -441,14 +441,18 @@ __device__ __forceinline__ void general_segment(ConstParams p, int sl, int tile,
   float rref[NPX];
 #pragma unroll
   for (int i = 0; i < NPX; ++i) rref[i] = Rl[(hy + RAD) * DW + hx0 + RAD + i];
-  store_pixels(out, sl, ty0 + hy, tx0 + hx0, win, Wl + tid, Uacc, Pacc, rref, 0.f);
+  store_pixels(out, sl, ty0 + hy, tx0 + hx0, win, Wl + tid, Uacc, Pacc, rref, 1.0, 0.f);
 }
 
 // One (segment sl, tile) work item of one recording in fixed point; false if
 // it is one for the general path.
+template <bool BATCH>
 __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int tile, Smem& sm) {
   float4* Wl = sm.Wl;
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  // what follows from the thread's number is formed anew for each item rather
+  // than kept in scratch around the batch kernel's loop
+  if constexpr (BATCH) asm volatile("" : "+v"(tid));
   const int lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const Out out = outputs(params);
@@ -662,13 +666,17 @@ __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int ti
         const int o = k + 2 - b;
         if (o >= 0 && o < 4) s[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wb[o], y[b], s[k], 0, 0, 0);
       }
-    const float unit = __builtin_ldexpf(1.f, 16 - kFrac - wbits - x);
     float o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const double hi = (double)((s[5][i] << 8) + s[4][i]), mid = (double)((s[3][i] << 8) + s[2][i]),
                    lo = (double)((s[1][i] << 8) + s[0][i]);
-      o[i] = (float)fma(fma(hi, 65536.0, mid), 65536.0, lo) * unit;
+      o[i] = (float)fma(fma(hi, 65536.0, mid), 65536.0, lo);
+    }
+    if (x != e) {   // in units of the tile's scale
+      const float by = __builtin_ldexpf(1.f, e - x);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] *= by;
     }
     return make_float4(o[0], o[1], o[2], o[3]);
   };
@@ -731,7 +739,8 @@ __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int ti
   const uint2 rr = *reinterpret_cast<const uint2*>(&sm.r16[hy * (TW / 2) + hx0 / 2]);
   const float rref[NPX] = {(float)(rr.x & 0xffffu), (float)(rr.x >> 16), (float)(rr.y & 0xffffu), (float)(rr.y >> 16)};
   const float quiet = params->quiet * __builtin_ldexpf(1.f, -least);
-  if (store_pixels(out, sl, ty0 + hy, tx0 + hx0, win, Wl + tid, Uacc, Pacc, rref, quiet))
+  if (store_pixels(out, sl, ty0 + hy, tx0 + hx0, win, Wl + tid, Uacc, Pacc, rref,
+                   __builtin_ldexp(1.0, 16 - kFrac - wbits - e), quiet))
     sm.leave[NCH] = 1;
   __syncthreads();
   return !__builtin_amdgcn_readfirstlane(sm.leave[NCH]);
@@ -752,11 +761,11 @@ __device__ __attribute__((noinline)) void general_call(ConstParams params, int s
                           *(Smem*)(LdsSmem)(uintptr_t)at);
 }
 
-template <bool CALL>
+template <bool BATCH>
 __device__ __forceinline__ void work_item(ConstParams params, int sl, int tile, Smem& sm) {
-  if (fixed_segment(params, sl, tile, sm)) return;
+  if (fixed_segment<BATCH>(params, sl, tile, sm)) return;
   if (params->W < 4) general_call<true>(params, sl, tile, (LdsSmem)&sm);
-  else if (CALL) general_call<false>(params, sl, tile, (LdsSmem)&sm);
+  else if (BATCH) general_call<false>(params, sl, tile, (LdsSmem)&sm);
   else general_segment<false>(params, sl, tile, sm);
 }
 
