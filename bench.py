@@ -497,7 +497,7 @@ def main():
                "hbm_frac": bytes_alg / seconds / HBM_PEAK}
         if kernel == "k_block_stats":
             out["note"] = ("the algorithm's operations (two 25-tap passes) against the FP64 peak; the kernel forms "
-                           "them as exact byte products on INT8 MFMA")
+                           "them in fixed point, as byte products on INT8 MFMA")
         return out
 
     # voltage traces (the stage after segmentation) of the resident video,

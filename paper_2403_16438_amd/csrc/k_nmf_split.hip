@@ -634,19 +634,19 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
                 const int q = e / K, i = e - q * K;
                 const int m1 = min(ml, (q + 1) * rows);
                 double s0[NR], s1[NR];
-  #pragma unroll
+#pragma unroll
                 for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
                 int m = q * rows;
                 if constexpr (NR <= 3) {   // four rows' reads in flight
                   for (; m + 3 < m1; m += 4) {
                     double p[4], f[4][NR];
-  #pragma unroll
+#pragma unroll
                     for (int u = 0; u < 4; ++u) {
                       p[u] = (double)Pl[(m + u) * Kp + i];
-  #pragma unroll
+#pragma unroll
                       for (int n = 0; n < NR; ++n) f[u][n] = F[(m + u) * R8 + n];
                     }
-  #pragma unroll
+#pragma unroll
                     for (int n = 0; n < NR; ++n) {
                       s0[n] = fma(f[0][n], p[0], s0[n]);
                       s1[n] = fma(f[1][n], p[1], s1[n]);
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
                 }
                 for (; m + 1 < m1; m += 2) {
                   const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[(m + 1) * Kp + i];
-  #pragma unroll
+#pragma unroll
                   for (int n = 0; n < NR; ++n) {
                     s0[n] = fma(F[m * R8 + n], p0, s0[n]);
                     s1[n] = fma(F[(m + 1) * R8 + n], p1, s1[n]);
@@ -665,10 +665,10 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
                 }
                 if (m < m1) {
                   const double p0 = (double)Pl[m * Kp + i];
-  #pragma unroll
+#pragma unroll
                   for (int n = 0; n < NR; ++n) s0[n] = fma(F[m * R8 + n], p0, s0[n]);
                 }
-  #pragma unroll
+#pragma unroll
                 for (int n = 0; n < NR; ++n) {
                   if (QC == 1) put(ex, (size_t)n * K + i, s0[n] + s1[n]);
                   else scr[(size_t)e * NR + n] = s0[n] + s1[n];
@@ -707,21 +707,21 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
           // ---- the A update (rows of A in order), every workgroup alike
           for (int i = t; i < K; i += CT) {
             double av[NR];
-  #pragma unroll
+#pragma unroll
             for (int n = 0; n < NR; ++n) av[n] = A[i * R8 + n];
-  #pragma unroll
+#pragma unroll
             for (int n = 0; n < NR; ++n) {
               // from rank 6 on, hoisting all Gram reads would spill: keep them per row
               if constexpr (NR > 5) asm volatile("" ::: "memory");
               const double d = gF[n * R8 + n];
               if (d > 0.0) {
                 double sg = 0.0;
-  #pragma unroll
+#pragma unroll
                 for (int n2 = 0; n2 < NR; ++n2) sg += gF[n * R8 + n2] * av[n2];
                 av[n] = fmax(0.0, av[n] + (FtP[n * K + i] - sg) / d);
               }
             }
-  #pragma unroll
+#pragma unroll
             for (int n = 0; n < NR; ++n) A[i * R8 + n] = av[n];
           }
           __syncthreads();
@@ -739,12 +739,12 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
                 const int q = e / ml, m = e - q * ml;
                 const int i1 = min(K, (q + 1) * seg);
                 double s0[NR], s1[NR];
-  #pragma unroll
+#pragma unroll
                 for (int n = 0; n < NR; ++n) s0[n] = s1[n] = 0.0;
                 int i = q * seg;
                 for (; i + 1 < i1; i += 2) {
                   const double p0 = (double)Pl[m * Kp + i], p1 = (double)Pl[m * Kp + i + 1];
-  #pragma unroll
+#pragma unroll
                   for (int n = 0; n < NR; ++n) {
                     s0[n] = fma(p0, A[i * R8 + n], s0[n]);
                     s1[n] = fma(p1, A[(i + 1) * R8 + n], s1[n]);
@@ -752,10 +752,10 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
                 }
                 if (i < i1) {
                   const double p0 = (double)Pl[m * Kp + i];
-  #pragma unroll
+#pragma unroll
                   for (int n = 0; n < NR; ++n) s0[n] = fma(p0, A[i * R8 + n], s0[n]);
                 }
-  #pragma unroll
+#pragma unroll
                 for (int n = 0; n < NR; ++n) scr[(size_t)e * NR + n] = s0[n] + s1[n];
               }
             } else {   // A A^T, upper triangle mirrored (every workgroup alike)
@@ -773,23 +773,23 @@ __global__ __launch_bounds__(ROWS ? 512 : 1024) void k_nmf_split(NmfArgs a, NmfS
           // its row's P A^T chunks in order first
           for (int m = t; m < ml; m += CT) {
             double gp[NR], f[NR];
-  #pragma unroll
+#pragma unroll
             for (int n = 0; n < NR; ++n) {
               gp[n] = chunk_sum(scr + (size_t)m * NR + n, (size_t)ml * NR, QK);   // P A^T: chunks in order
               f[n] = F[m * R8 + n];
             }
-  #pragma unroll
+#pragma unroll
             for (int n = 0; n < NR; ++n) {
               if constexpr (NR > 5) asm volatile("" ::: "memory");
               const double d = gA[n * R8 + n];
               if (d > 0.0) {
                 double sg = 0.0;
-  #pragma unroll
+#pragma unroll
                 for (int n2 = 0; n2 < NR; ++n2) sg += f[n2] * gA[n2 * R8 + n];
                 f[n] = fmax(0.0, f[n] + (gp[n] - sg) / d);
               }
             }
-  #pragma unroll
+#pragma unroll
             for (int n = 0; n < NR; ++n) F[m * R8 + n] = f[n];
           }
           __syncthreads();

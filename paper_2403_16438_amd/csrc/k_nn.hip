@@ -1154,9 +1154,8 @@ __global__ void k_im2col3_v(const float* __restrict__ X, uint16_t* __restrict__ 
   *reinterpret_cast<uint4*>(col + (long long)r * N + p) = pk;
 }
 
-// dX[c][b][y][x] (+)= sum_{ky,kx} dcol[c*9 + ky*3 + kx][b, y - ky + 1, x - kx + 1]
-__global__ void k_col2im3(const float* __restrict__ dcol, float* __restrict__ dX, int C, int Bn, int H, int W,
-                          int accumulate) {
+// dX[c][b][y][x] = sum_{ky,kx} dcol[c*9 + ky*3 + kx][b, y - ky + 1, x - kx + 1]
+__global__ void k_col2im3(const float* __restrict__ dcol, float* __restrict__ dX, int C, int Bn, int H, int W) {
   const long long N = (long long)Bn * H * W;
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N * C) return;
@@ -1170,7 +1169,7 @@ __global__ void k_col2im3(const float* __restrict__ dcol, float* __restrict__ dX
       if (yy >= 0 && yy < H && xx >= 0 && xx < W)
         s += dcol[(long long)(c * 9 + ky * 3 + kx) * N + (long long)b * H * W + yy * W + xx];
     }
-  dX[i] = accumulate ? dX[i] + s : s;
+  dX[i] = s;
 }
 
 // -------------------------------------------------- temporal convolutions
@@ -1836,8 +1835,8 @@ void im2col3(const float* X, uint16_t* col, int C, int Bn, int H, int W, hipStre
   else
     L1(k_im2col3, (long long)C * 9 * Bn * H * W, X, col, C, Bn, H, W);
 }
-void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, bool acc, hipStream_t st) {
-  L1(k_col2im3, (long long)C * Bn * H * W, dcol, dX, C, Bn, H, W, (int)acc);
+void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, hipStream_t st) {
+  L1(k_col2im3, (long long)C * Bn * H * W, dcol, dX, C, Bn, H, W);
 }
 void tnorm(const uint16_t* frames, float* out, int Bn, int L, long long HW, hipStream_t st) {
   L1(k_tnorm, (long long)Bn * HW, frames, out, Bn, L, HW);

@@ -380,7 +380,7 @@ hipError_t conv3_bwd(seg_nn* n, Grads& g, int id, const float* X, const float* d
   g.reduce(st);
   float* dcol = at<float>(n, n->plan.dcol);
   e = gemm_wtdy(n, id, dY, N, dcol, st);
-  col2im3(dcol, dX, Ci, Bn, H, W, false, st);
+  col2im3(dcol, dX, Ci, Bn, H, W, st);
   return e;
 }
 

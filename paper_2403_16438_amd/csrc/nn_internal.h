@@ -111,7 +111,7 @@ struct ReorderTable {
 };
 void conv3_reorder(ReorderTable& t, hipStream_t st);
 size_t conv3_reordered_size(int Co, int Ci);
-void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, bool acc, hipStream_t st);
+void col2im3(const float* dcol, float* dX, int C, int Bn, int H, int W, hipStream_t st);
 void tnorm(const uint16_t* frames, float* out, int Bn, int L, long long HW, hipStream_t st);
 void im2col1(const float* in, uint16_t* col, int C, int Tin, int Tout, int KT, int S, int P, long long N,
              hipStream_t st);
