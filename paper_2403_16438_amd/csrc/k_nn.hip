@@ -1534,11 +1534,14 @@ __global__ void k_to_bf16(const float* __restrict__ w, uint16_t* __restrict__ wb
 
 // FP64 mean and population deviation of S, then channel 0 = (S - mean) /
 // max(sd, 1e-3), channel 1 = T / sqrt(S + 25). The FP64 divisions and square
-// roots of the pixels are the work: NORM_Q blocks of 1,024 threads per patch
+// roots of the pixels are the work: gridDim.y blocks of 1,024 threads per patch
 // each form the patch's sums (alike, in one order) and normalise their part of
-// its pixels (49 patches of 64 x 64: 7.2 us with one block per patch,
-// 5.8 with four).
-constexpr int NORM_NT = 1024, NORM_Q = 4;
+// its pixels. Four per patch while that is no more than a block per compute
+// unit, then two, then one, since each reads the whole patch: patches of 64 x 64
+// with one, two and four take 6.8, 6.0 and 5.4 us (49 of them), 6.8, 5.4 and 5.2
+// (64), 6.8, 5.7 and 6.6 (80), 7.2, 6.2 and 7.2 (128), 9.0, 9.8 and 13.0 (200),
+// 13.2, 16.8 and 22.1 (392).
+constexpr int NORM_NT = 1024;
 __global__ __launch_bounds__(NORM_NT) void k_st_norm(const float* __restrict__ stin, float* __restrict__ x, int Bn,
                                                      long long HW) {
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -1572,7 +1575,7 @@ __global__ __launch_bounds__(NORM_NT) void k_st_norm(const float* __restrict__ s
   }
   const double m = __shfl(s, 0, 64) / (double)HW;
   const double sd = fmax(sqrt(fmax(__shfl(s2, 0, 64) / (double)HW - m * m, 0.0)), 1e-3);
-  for (long long i = (long long)blockIdx.y * NORM_NT + tid; i < HW; i += NORM_NT * NORM_Q) {
+  for (long long i = (long long)blockIdx.y * NORM_NT + tid; i < HW; i += (long long)NORM_NT * gridDim.y) {
     x[(size_t)b * HW + i] = (float)(((double)S[i] - m) / sd);
     x[((size_t)Bn + b) * HW + i] = (float)((double)T[i] / sqrt(fmax((double)S[i], 0.0) + 25.0));
   }
@@ -1874,7 +1877,7 @@ void rmsprop(float* w, const float* g, float* v, uint16_t* wb, long long n, floa
 void to_bf16_copy(const float* w, uint16_t* wb, long long n, hipStream_t st) { L1(k_to_bf16, n, w, wb, n); }
 
 void st_norm(const float* stin, float* x, int Bn, long long HW, hipStream_t stream) {
-  hipLaunchKernelGGL(k_st_norm, dim3((unsigned)Bn, NORM_Q), dim3(NORM_NT), 0, stream, stin, x, Bn, HW);
+  hipLaunchKernelGGL(k_st_norm, dim3((unsigned)Bn, Bn <= 64 ? 4 : Bn <= 128 ? 2 : 1), dim3(NORM_NT), 0, stream, stin, x, Bn, HW);
 }
 int st_origins(int n) { return (n - 64 + 31) / 32 + 1; }
 void st_patches(const float* S, const float* T, int H, int W, float* out, hipStream_t st) {
