@@ -27,8 +27,8 @@
 //
 // Accuracy: a smoothed value has one rounding to 2^-(28 + e) and one to FP32,
 // where FP64 sums with an FP32 intermediate have two to FP32. The first is the
-// smaller error in T from T = 0.1 sqrt(sum w^2) 2^-e on (0.03 at sigma 3 and
-// e = 0: noise of sd 0.14). A segment of a tile with a fainter pixel among those
+// smaller error in T from T = 0.1 sqrt(sum w^2) 2^-e on, e the smallest of the
+// segment's frames (0.03 at sigma 3 and e = 0: noise of sd 0.14). A segment of a tile with a fainter pixel among those
 // whose own values vary, one with |d| above 32,000 and frames narrower than four
 // pixels take the general path: FP64 sums over 25 taps in both passes. (A pixel
 // that is constant itself and sees others' noise at the kernel's edge keeps the
@@ -45,12 +45,12 @@
 // matrix operands read them, and one barrier per frame with the three steps
 // of three frames between two. Measured, from FP64 sums and two barriers per
 // frame (which also read a width that is no multiple of four pixel by pixel):
-// 64 x 64 x 50 99 -> 81 us, 450 x 138 x 500 561 -> 171 us, four recordings of
-// 500 frames in one launch (128 x 128 to 512 x 512) 1,520 -> 1,005 us (the four
-// bytes above: 80, 168 and 1,000 us). 256 x 256 x 1,600: 578 -> 455 us, the same
-// with bright frames in every segment, and 582 -> 587 us with values over the whole 16-bit range
-// (138 x 450 x 500 487 -> 212 us),
-// which takes the general path.
+// 64 x 64 x 50 99 -> 81 us, 450 x 138 x 500 561 -> 172 us, four recordings of
+// 500 frames in one launch (128 x 128 to 512 x 512) 1,515 -> 934 us (the four
+// bytes above: 80, 168 and 1,000 us). 256 x 256 x 1,600: 586 -> 449 us, with
+// bright frames in every segment 573 -> 438 us, and with values over the whole
+// 16-bit range, which take the general path, 578 -> 577 us (138 x 450 x 500 490
+// -> 220 us).
 //
 // Every thread owns 4 adjacent pixels of one tile row and keeps their 50
 // smoothed values in VGPRs (40) and a per-thread LDS slot (the chunk being
@@ -325,7 +325,7 @@ __device__ __forceinline__ bool store_pixels(const Out& p, int sl, int gy, int g
 // The general path: FP64 sums of d in FP32, from the segment's first frame, so
 // that no register lives on from the fixed-point path: with its window and
 // scale handed over in one body, frames that all come here took 660 us at
-// 256 x 256 x 1,600 (now 587). NARROW: rows of fewer than four pixels.
+// 256 x 256 x 1,600 (now 577). NARROW: rows of fewer than four pixels.
 template <bool NARROW>
 __device__ __forceinline__ void general_segment(ConstParams p, int sl, int tile, Smem& sm) {
   const Out out = outputs(p);
@@ -750,7 +750,7 @@ __device__ __forceinline__ bool fixed_segment(ConstParams params, int sl, int ti
 // compiler is to know that the LDS is aligned (four-byte LDS reads otherwise:
 // 625 -> 655 us). The batch kernel, short of registers for its loop over items,
 // and narrow frames call it; a call saves 112 registers per thread, and where
-// all segments take it costs 610 us instead of 587.
+// all segments take it costs 25 us more.
 template <bool NARROW>
 __device__ __attribute__((noinline)) void general_call(ConstParams params, int sl, int tile, LdsSmem lds) {
   const uint64_t p = (uint64_t)params;
